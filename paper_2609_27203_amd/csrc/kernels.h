@@ -272,6 +272,16 @@ hipError_t remap_codes(uint32_t* col, int64_t n, const uint32_t* map, hipStream_
 // Values of n int32 images into out (1, 4 or 8 bytes each by ltype); dict
 // holds the order keys of the 8-byte types.
 hipError_t decode_column(const uint32_t* img, int64_t n, int ltype, const u64* dict, void* out, hipStream_t s);
+// The same for ncols columns of n images each in one launch: dst[j] (aligned
+// to the element size of ltype[j]) receives column j in row order.  i32 and
+// f32 columns are copied.
+struct ReadCols {
+  const uint32_t* src[MAXC];
+  void* dst[MAXC];
+  const u64* dict[MAXC];
+  int ltype[MAXC];
+};
+hipError_t read_columns(const ReadCols& r, int ncols, int64_t n, hipStream_t s);
 
 }  // namespace k
 }  // namespace xlh
