@@ -361,6 +361,23 @@ struct GatherArgs {
 };
 
 
+// One round of h(X,Y) :- h(X,Z), h(Z,Y) over a dense set head whose rows are
+// bitmaps: next(x) = (OR of full(z) for z in delta(x), OR of delta(z) for z in
+// full(x)) minus full(x).  Bit b of a row is the value z of bitmap row
+// b + zoff (when that lies in [0, range0)).
+struct SelfJoinArgs {
+  const uint32_t* full;       // [range0][row_words] the relation as the round began
+  const uint32_t* delta;      // [range0][row_words]
+  uint32_t* next;             // [range0][row_words] next delta (written whole)
+  const uint32_t* full_cnt;   // [range0] set bits of each row
+  const uint32_t* delta_cnt;  // [range0]
+  uint32_t* next_cnt;         // [range0]
+  int64_t range0, zoff;
+  uint32_t row_words;
+  const unsigned long long* prev;  // CNT_APPENDED of the round before (null: none); 0 = nothing to do
+  unsigned long long* counters;    // CNT_CANDIDATES, CNT_APPENDED
+};
+
 // Worst-case-optimal triangle join (count -> scan -> materialize).  Driver
 // rows (x, y) come from a's index in (X, Y) order; b is indexed by its Y
 // column and c by its X column, each with the rows of one key sorted by the

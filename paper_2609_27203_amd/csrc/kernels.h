@@ -165,6 +165,13 @@ hipError_t frontier_round(const FrontierArgs& a, hipStream_t s);
 hipError_t frontier_resident(const FrontierArgs& a, unsigned grid, hipStream_t s);
 // One gathered round (see GatherArgs).
 hipError_t gather_round(const GatherArgs& a, hipStream_t s);
+// One round of a self-joined closure (see SelfJoinArgs; row_words at most
+// SJ_MAX_WORDS, else hipErrorInvalidValue), then full |= next and full_cnt +=
+// next_cnt (neither does anything when *prev is 0; prev may be null).
+constexpr uint32_t SJ_MAX_WORDS = 512;
+hipError_t self_join_round(const SelfJoinArgs& a, hipStream_t s);
+hipError_t self_join_merge(uint32_t* full, const uint32_t* next, int64_t nwords, uint32_t* full_cnt,
+                           const uint32_t* next_cnt, const u64* prev, int64_t nrows, hipStream_t s);
 // Zero the flagged rows of a [nrows][row_words] bitmap and their flags.
 hipError_t clear_flagged_rows(uint32_t* bits, uint32_t* flag, int64_t nrows, uint32_t row_words, uint32_t* lo,
                               uint32_t* hi, hipStream_t s);
