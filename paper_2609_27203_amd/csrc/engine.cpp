@@ -712,12 +712,11 @@ struct Runner {
       if (e) (void)hipEventDestroy(e);
   }
 
-  // Slots of a dense value head's full relation and their layout (0: rank
-  // major, n: target-major with n ranks per target, as sum/logsumexp heads).
+  // Slots of a dense value head's full relation (rank-major; sum/logsumexp
+  // heads target-major, nrank_d ranks per target).
   static int64_t full_slots(const HeadRun* h) {
     return h->ds ? h->nrank_d * h->range1 : std::max<int64_t>(h->n0, 1) * h->range1;
   }
-  static uint32_t full_nrank(const HeadRun* h) { return h->ds ? (uint32_t)h->nrank_d : 0u; }
 
   HeadRun* head_of(const Relation* r) {
     for (auto& h : heads)
@@ -836,7 +835,7 @@ struct Runner {
         uint32_t* k1 = h->nkey == 2 ? (uint32_t*)snap[1] : nullptr;
         if (h->dv)
           HIP_TRY(c, k::dense_rows(h->dvals.as<uint32_t>(), h->dpres.as<uint32_t>(), h->dict.as<uint32_t>(), ns,
-                                   h->range1, full_nrank(h), h->kp, rel->types[h->nkey], h->fold, (uint32_t*)snap[0], k1,
+                                   h->range1, h->kp, rel->types[h->nkey], h->fold, (uint32_t*)snap[0], k1,
                                    (uint32_t*)snap[h->nkey], std::max<int64_t>(n, 1), tot.as<uint32_t>(), tmp.p,
                                    c->stream));
         else
@@ -3614,21 +3613,29 @@ struct Runner {
     if (h->dv) {
       const int64_t n = h->keys;
       const int64_t ns = full_slots(h);
+      for (Buf* b : {&h->dcur, &h->dnext, &h->ndrow[0], &h->ndrow[1], &h->ndrow[2]}) b->reset();  // rounds are over
       Buf out[3], tmp, tot;
       for (int j = 0; j <= h->nkey; ++j) XL_TRY(dalloc(c, (size_t)std::max<int64_t>(n, 1) * 4, &out[j], "relation column"));
-      XL_TRY(dalloc(c, k::compact_temp_bytes(ns), &tmp, "compaction scratch"));
+      XL_TRY(dalloc(c, h->ds ? k::target_rows_temp_bytes(h->range1, h->nrank_d) : k::compact_temp_bytes(ns), &tmp,
+                    "compaction scratch"));
       XL_TRY(dalloc(c, 8, &tot, "count"));
-      HIP_TRY(c, k::dense_rows(h->dvals.as<uint32_t>(), h->dpres.as<uint32_t>(), h->dict.as<uint32_t>(), ns,
-                               h->range1, full_nrank(h), h->kp, r->types[h->nkey], h->fold, out[0].as<uint32_t>(),
-                               h->nkey == 2 ? out[1].as<uint32_t>() : nullptr, out[h->nkey].as<uint32_t>(),
-                               std::max<int64_t>(n, 1), tot.as<uint32_t>(), tmp.p, c->stream));
+      if (h->ds)
+        HIP_TRY(c, k::target_rows(h->dvals.as<uint32_t>(), h->dpres.as<uint32_t>(), h->dict.as<uint32_t>(), h->n0,
+                                  h->range1, h->nrank_d, h->kp, r->types[h->nkey], h->fold, out[0].as<uint32_t>(),
+                                  out[1].as<uint32_t>(), out[2].as<uint32_t>(), std::max<int64_t>(n, 1),
+                                  tot.as<uint32_t>(), tmp.p, c->stream));
+      else
+        HIP_TRY(c, k::dense_rows(h->dvals.as<uint32_t>(), h->dpres.as<uint32_t>(), h->dict.as<uint32_t>(), ns,
+                                 h->range1, h->kp, r->types[h->nkey], h->fold, out[0].as<uint32_t>(),
+                                 h->nkey == 2 ? out[1].as<uint32_t>() : nullptr, out[h->nkey].as<uint32_t>(),
+                                 std::max<int64_t>(n, 1), tot.as<uint32_t>(), tmp.p, c->stream));
       uint32_t m = 0;
       XL_TRY(ctl_read(c, tot.p, 4, &m));
       if ((int64_t)m != n) return c->fail(XL_DEVICE_ERROR, "dense value count mismatch (internal)");
       relation_free_storage(r);
       for (int j = 0; j <= h->nkey; ++j) r->col[j] = (uint32_t*)out[j].keep();
       r->nrows = n;
-      r->sorted = !h->ds;  // rank-major slots ascend with the keys
+      r->sorted = true;  // rows rank by rank: ascending keys
     } else if (h->is_set) {
       relation_free_storage(r);
       for (int j = 0; j < h->nkey; ++j) r->col[j] = (uint32_t*)h->rows[j].keep();

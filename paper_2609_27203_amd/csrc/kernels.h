@@ -186,11 +186,18 @@ hipError_t bits_to_rows(const uint32_t* bits, int64_t nrows, uint32_t row_words,
 hipError_t gather_rows(const uint32_t* bits, uint32_t row_words, const uint32_t* x, int32_t lo0, int64_t nseg,
                        uint32_t* out, hipStream_t s);
 // Dense value heads (first key through a dictionary, second key direct).
-// Rows of every present slot in slot order (= ascending keys).
-// nrank = 0: slot rank * range1 + (y - lo1); nrank > 0: slot (y - lo1) * nrank + rank.
+// Rows of every present slot rank * range1 + (y - lo1) in slot order (=
+// ascending keys).
 hipError_t dense_rows(const uint32_t* vals, const uint32_t* pres, const uint32_t* dict, int64_t n,
-                      int64_t range1, int64_t nrank, KeyPack kp, int type, int fold_kind, uint32_t* k0, uint32_t* k1,
+                      int64_t range1, KeyPack kp, int type, int fold_kind, uint32_t* k0, uint32_t* k1,
                       uint32_t* v, int64_t out_cap, uint32_t* total, void* temp, hipStream_t s);
+// The same over slots (y - lo1) * nrank + rank (nrank a multiple of 32, n0
+// ranks in use, range1 * nrank < 2^32): the rows also come in ascending keys.
+// temp: target_rows_temp_bytes(range1, nrank).
+size_t target_rows_temp_bytes(int64_t range1, int64_t nrank);
+hipError_t target_rows(const uint32_t* vals, const uint32_t* pres, const uint32_t* dict, int64_t n0, int64_t range1,
+                       int64_t nrank, KeyPack kp, int type, int fold_kind, uint32_t* k0, uint32_t* k1, uint32_t* v,
+                       int64_t out_cap, uint32_t* total, void* temp, hipStream_t s);
 hipError_t dict_mark(const uint32_t* col, int64_t n, int32_t lo, uint32_t range, uint32_t* mark, hipStream_t s);
 hipError_t dict_finish(uint32_t* map, const uint32_t* pos, uint32_t range, int32_t lo, uint32_t* dict,
                        hipStream_t s);

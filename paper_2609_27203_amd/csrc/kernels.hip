@@ -1123,7 +1123,6 @@ struct CompactArgs {
   KeyPack kp;
   int type, fold_kind;
   int64_t range1;         // CK_COUNTER: second-key range
-  int64_t nrank;          // CK_DENSE: 0 = slot rank * range1 + y, else slot y * nrank + rank
   uint32_t* k0;           // CK_NONEMPTY / CK_COUNTER rows; CK_STAMP: slot indices
   uint32_t* k1;
   uint32_t* v;
@@ -1160,8 +1159,7 @@ __global__ __launch_bounds__(CP_THREADS) void compact_write_k(CompactArgs a) {
   const int64_t base = (int64_t)blockIdx.x * a.rlen;
   const int w = threadIdx.x >> 6;
   // dense slots below 2^32 (the dense forms' limit) split with 32-bit division
-  const bool narrow = a.n <= (int64_t)0xffffffffll && a.nrank <= (int64_t)0xffffffffll &&
-                      a.range1 <= (int64_t)0xffffffffll;
+  const bool narrow = a.n <= (int64_t)0xffffffffll && a.range1 <= (int64_t)0xffffffffll;
   uint32_t out = a.range_off[blockIdx.x];
   for (int64_t k = 0; k < a.rlen / CP_THREADS; ++k) {
     const int64_t i = base + k * CP_THREADS + threadIdx.x;
@@ -1184,13 +1182,12 @@ __global__ __launch_bounds__(CP_THREADS) void compact_write_k(CompactArgs a) {
       } else if (a.kind == CK_DENSE) {
         int64_t rk, yb;
         if (narrow) {
-          const uint32_t i32 = (uint32_t)i, d = (uint32_t)(a.nrank ? a.nrank : a.range1);
-          const uint32_t q = i32 / d, r = i32 - q * d;
-          rk = a.nrank ? r : q;
-          yb = a.nrank ? q : r;
+          const uint32_t i32 = (uint32_t)i, d = (uint32_t)a.range1;
+          rk = i32 / d;
+          yb = i32 - (uint32_t)rk * d;
         } else {
-          rk = a.nrank ? i % a.nrank : i / a.range1;
-          yb = a.nrank ? i / a.nrank : i % a.range1;
+          rk = i / a.range1;
+          yb = i % a.range1;
         }
         a.k0[p] = a.dict[rk];
         if (a.k1) a.k1[p] = (uint32_t)yb + (uint32_t)a.kp.lo[1];
@@ -1285,11 +1282,10 @@ hipError_t dcount_rows(const uint32_t* counts, int64_t n, int64_t range1, KeyPac
 }
 
 hipError_t dense_rows(const uint32_t* vals, const uint32_t* pres, const uint32_t* dict, int64_t n,
-                      int64_t range1, int64_t nrank, KeyPack kp, int type, int fold_kind, uint32_t* k0, uint32_t* k1,
+                      int64_t range1, KeyPack kp, int type, int fold_kind, uint32_t* k0, uint32_t* k1,
                       uint32_t* v, int64_t out_cap, uint32_t* total, void* temp, hipStream_t s) {
   CompactArgs a{};
   a.kind = CK_DENSE;
-  a.nrank = nrank;
   a.counts = vals;
   a.pres = pres;
   a.dict = dict;
@@ -1303,6 +1299,129 @@ hipError_t dense_rows(const uint32_t* vals, const uint32_t* pres, const uint32_t
   a.v = v;
   a.out_cap = out_cap;
   return compact_run(a, total, temp, s);
+}
+
+// Rows of a target-major value head (slot y * nrank + rank, nrank a multiple
+// of 32) in canonical order, rank by rank: a transposition of the slots.  A
+// wavefront takes 32 ranks (one presence word per target) of a tile of
+// targets, lanes over targets.  The count pass ranks each rank's bits by
+// ballots and writes cnt[rank][tile]; after the scan of those counts the write
+// pass reads 64 x 32 values at a time (16-byte loads, 128 bytes per target),
+// turns them in LDS and writes each rank's rows with consecutive lanes on
+// consecutive positions.  Bound by its traffic (every slot read once, 12 bytes
+// written per row).  The rows need no sort when they are read, nor by a later
+// join on the first column: 256 sources x 100,000 targets, 20 M rows: 0.089 ms
+// both passes (3.9 TB/s in the write pass), where writing them in slot order
+// took 0.160 and the read's sort 4.3.
+constexpr int TR_WAVES = 4;
+constexpr int64_t TR_SCAN = 131072;  // counts kept within the one-launch scan where 64-target steps allow
+
+struct TargetRows {
+  const uint32_t* vals;
+  const uint32_t* pres;
+  const uint32_t* dict;
+  uint32_t n0, wpr, range1, steps, nt;  // ranks, words per target, targets, 64-target steps per tile, tiles
+  uint32_t lo1;
+  int type, fold_kind;
+  uint32_t* cnt;        // [32 * wpr][nt]
+  const uint32_t* off;  // its exclusive scan
+  uint32_t *k0, *k1, *v;
+  u64 out_cap;
+};
+
+template <bool WRITE>
+__global__ __launch_bounds__(TR_WAVES * 64) void target_rows_k(TargetRows a) {
+  __shared__ uint32_t s_tile[WRITE ? TR_WAVES : 1][32][65];
+  const uint32_t lane = (uint32_t)lane_id(), w = threadIdx.x >> 6;
+  const uint32_t id = blockIdx.x * TR_WAVES + w;
+  if (id >= a.nt * a.wpr) return;  // (no workgroup barriers below)
+  const uint32_t t = id / a.wpr, wc = id - t * a.wpr;
+  const u64 nrank = (u64)a.wpr * 32;
+  const uint32_t r = wc * 32 + lane;  // the rank lane < 32 keeps the running position of
+  uint32_t run = 0, key = 0;
+  if (WRITE && lane < 32) {
+    run = a.off[(u64)r * a.nt + t];
+    key = r < a.n0 ? a.dict[r] : 0u;
+  }
+  for (uint32_t st = 0; st < a.steps; ++st) {
+    const uint32_t y0 = (t * a.steps + st) * 64;
+    if (y0 >= a.range1) break;
+    const uint32_t y = y0 + lane;
+    const uint32_t word = y < a.range1 ? a.pres[(u64)y * a.wpr + wc] : 0u;
+    if (!__ballot(word != 0)) continue;
+    if (WRITE) {
+#pragma unroll
+      for (uint32_t i = 0; i < 8; ++i) {
+        const uint32_t idx = i * 64 + lane, yy = idx >> 3, q = (idx & 7u) * 4;
+        if (y0 + yy < a.range1) {
+          const uint4 x = *reinterpret_cast<const uint4*>(a.vals + (u64)(y0 + yy) * nrank + wc * 32 + q);
+          s_tile[w][q][yy] = x.x;
+          s_tile[w][q + 1][yy] = x.y;
+          s_tile[w][q + 2][yy] = x.z;
+          s_tile[w][q + 3][yy] = x.w;
+        }
+      }
+      wave_lds_sync();
+    }
+#pragma unroll 4
+    for (uint32_t b = 0; b < 32; ++b) {
+      const bool on = (word >> b) & 1u;
+      const u64 m = __ballot(on);
+      const uint32_t c = (uint32_t)__popcll(m);
+      if (WRITE) {
+        const uint32_t p = __shfl(run, (int)b, 64) + (uint32_t)__popcll(m & lanemask_lt());
+        const uint32_t x = __shfl(key, (int)b, 64);
+        if (on && p < a.out_cap) {
+          a.k0[p] = x;
+          a.k1[p] = y + a.lo1;
+          a.v[p] = stored_value(s_tile[w][b][lane], a.type, a.fold_kind);
+        }
+      }
+      if (lane == b) run += c;
+    }
+    if (WRITE) wave_lds_sync();
+  }
+  if (!WRITE && lane < 32) a.cnt[(u64)r * a.nt + t] = run;
+}
+
+static uint32_t target_steps(int64_t range1, int64_t nrank) {
+  return (uint32_t)std::max<int64_t>(1, (range1 * nrank + 64 * TR_SCAN - 1) / (64 * TR_SCAN));
+}
+size_t target_rows_temp_bytes(int64_t range1, int64_t nrank) {
+  const int64_t tile = 64 * (int64_t)target_steps(range1, nrank);
+  const int64_t n = nrank * ((range1 + tile - 1) / tile);
+  return (size_t)((n + 63) & ~63ll) * 8 + scan_temp_bytes(n) + 256;
+}
+hipError_t target_rows(const uint32_t* vals, const uint32_t* pres, const uint32_t* dict, int64_t n0, int64_t range1,
+                       int64_t nrank, KeyPack kp, int type, int fold_kind, uint32_t* k0, uint32_t* k1, uint32_t* v,
+                       int64_t out_cap, uint32_t* total, void* temp, hipStream_t s) {
+  if (range1 <= 0 || nrank <= 0 || (nrank & 31) || range1 * nrank > (int64_t)0xffffffffll) return hipErrorInvalidValue;
+  TargetRows a{};
+  a.vals = vals;
+  a.pres = pres;
+  a.dict = dict;
+  a.n0 = (uint32_t)n0;
+  a.wpr = (uint32_t)(nrank / 32);
+  a.range1 = (uint32_t)range1;
+  a.steps = target_steps(range1, nrank);
+  a.nt = (uint32_t)((range1 + 64 * (int64_t)a.steps - 1) / (64 * (int64_t)a.steps));
+  a.lo1 = (uint32_t)kp.lo[1];
+  a.type = type;
+  a.fold_kind = fold_kind;
+  const int64_t n = nrank * a.nt;
+  a.cnt = (uint32_t*)temp;
+  uint32_t* off = a.cnt + ((n + 63) & ~63ll);
+  a.off = off;
+  a.k0 = k0;
+  a.k1 = k1;
+  a.v = v;
+  a.out_cap = (u64)out_cap;
+  const unsigned grid = (a.nt * a.wpr + TR_WAVES - 1) / TR_WAVES;
+  target_rows_k<false><<<grid, TR_WAVES * 64, 0, s>>>(a);
+  hipError_t e = scan_exclusive_u32(a.cnt, off, n, total, (char*)(off + ((n + 63) & ~63ll)), s);
+  if (e != hipSuccess) return e;
+  target_rows_k<true><<<grid, TR_WAVES * 64, 0, s>>>(a);
+  return hipGetLastError();
 }
 
 // ---- first-key dictionaries ---------------------------------------------------
