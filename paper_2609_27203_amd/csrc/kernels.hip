@@ -293,13 +293,23 @@ hipError_t scan_exclusive_u64(const u64* in, u64* out, int64_t n, u64* total, vo
 }
 
 // ============================================================ radix sort
-// LSD radix sort with 8-bit digits.  Per pass: a per-tile digit histogram
-// (LDS atomics; the tile's counts are also added to the pass's 256 digit
-// totals), the digit-major offsets (one workgroup per digit scans that
-// digit's row of tile counts and adds the keys of all smaller digits), and a
-// stable scatter.  In the scatter each wavefront ranks its keys with a
-// ballot-based match of equal digits and running per-wave digit counters in
-// LDS, so the pass is stable without a block-wide sort.
+// LSD radix sort with 8-bit digits.  The keys are cut into tiles, and each of
+// at most RS_MAX_BLOCKS workgroups owns a run of consecutive tiles.  Per pass:
+// every workgroup counts its run's digits (LDS, one counter set per
+// wavefront); the digit-major offsets of those counts are formed; a stable
+// scatter walks the run's tiles with running digit positions.  In the scatter
+// each wavefront ranks its keys with a ballot-based match of equal digits and
+// per-wave digit counters in LDS, so the pass is stable without a block-wide
+// sort.
+// Bound by its traffic (keys read twice, keys and values written once) where
+// the input is large, by the launches where it is small:
+//  - counts go to a table, never to shared totals: adding each tile's counts
+//    to 256 device-wide totals cost more than the count itself (8 M pairs of
+//    32 bits: 33 us a pass, now 14; the scatter, at several tiles a workgroup,
+//    50 -> 40);
+//  - up to RS_DIRECT workgroups the scatter reads the whole table itself
+//    (at most 64 KB) and a pass is two launches; above it rs_offsets_k scans
+//    one digit's row per workgroup and the scatter adds the digit bases.
 // Tiles of RS_THREADS * ITEMS keys: 16 items per thread for large inputs,
 // 4 for small ones so that a few hundred thousand keys still spread over
 // every CU.
@@ -307,121 +317,157 @@ constexpr int RS_THREADS = 256;
 constexpr int RS_WAVES = RS_THREADS / 64;
 constexpr int RS_SMALL_ITEMS = 4;
 constexpr int64_t RS_SMALL_N = (int64_t)1 << 22;  // below this, small tiles
+constexpr int64_t RS_MAX_BLOCKS = 1024;           // four workgroups per CU
+constexpr uint32_t RS_DIRECT = 64;
 
+// hist[digit * sd + block * sb] = keys of the block's run with that digit.
 template <typename K, int RS_ITEMS>
-__global__ __launch_bounds__(RS_THREADS) void rs_hist_k(const K* keys, int64_t n, int shift,
-                                                         uint32_t dmask, uint32_t* hist,
-                                                         uint32_t nblocks, uint32_t* totals) {
+__global__ __launch_bounds__(RS_THREADS) void rs_hist_k(const K* keys, int64_t n, int shift, uint32_t dmask,
+                                                         uint32_t* hist, uint32_t sd, uint32_t sb, uint32_t tpb) {
   constexpr int RS_TILE = RS_THREADS * RS_ITEMS;
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0;
+  __shared__ uint32_t h[RS_WAVES][256];
+  const int w = threadIdx.x >> 6;
+  for (int i = threadIdx.x; i < RS_WAVES * 256; i += RS_THREADS) (&h[0][0])[i] = 0;
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * RS_TILE;
+  for (uint32_t t = 0; t < tpb; ++t) {
+    const int64_t base = ((int64_t)blockIdx.x * tpb + t) * RS_TILE;
+    if (base >= n) break;
+    K k[RS_ITEMS];
 #pragma unroll
-  for (int i = 0; i < RS_ITEMS; ++i) {
-    int64_t idx = base + (int64_t)i * RS_THREADS + threadIdx.x;
-    if (idx < n) atomicAdd(&h[(uint32_t)(keys[idx] >> shift) & dmask], 1u);
+    for (int i = 0; i < RS_ITEMS; ++i) {
+      const int64_t idx = base + (int64_t)i * RS_THREADS + threadIdx.x;
+      k[i] = idx < n ? keys[idx] : (K)0;
+    }
+#pragma unroll
+    for (int i = 0; i < RS_ITEMS; ++i) {
+      const int64_t idx = base + (int64_t)i * RS_THREADS + threadIdx.x;
+      if (idx < n) atomicAdd(&h[w][(uint32_t)(k[i] >> shift) & dmask], 1u);
+    }
   }
   __syncthreads();
-  const uint32_t c = h[threadIdx.x];
-  hist[(size_t)threadIdx.x * nblocks + blockIdx.x] = c;
-  if (c) atomicAdd(&totals[threadIdx.x], c);
+  uint32_t c = 0;
+#pragma unroll
+  for (int j = 0; j < RS_WAVES; ++j) c += h[j][threadIdx.x];
+  hist[(size_t)threadIdx.x * sd + (size_t)blockIdx.x * sb] = c;
 }
 
-// Workgroup d: row d of the histogram table (digit d's count in each tile)
-// becomes digit d's output offset in each tile: the number of keys with a
-// smaller digit plus digit d's count in the earlier tiles.  Workgroup 0 also
-// clears the digit totals of the next pass.
-__global__ __launch_bounds__(RS_THREADS) void rs_offsets_k(uint32_t* hist, uint32_t nblocks,
-                                                           const uint32_t* totals, uint32_t* next_totals) {
+// Workgroup d: row d of the digit-major table (digit d's count in each
+// block's run) becomes its exclusive prefix; totals[d] = the row's sum.
+__global__ __launch_bounds__(RS_THREADS) void rs_offsets_k(uint32_t* hist, uint32_t nblocks, uint32_t* totals) {
   __shared__ uint32_t s_w[RS_THREADS / 64];
-  __shared__ uint32_t s_base;
-  const uint32_t d = blockIdx.x;
-  uint32_t t;
-  const uint32_t below = block_excl_scan_u32(totals[threadIdx.x], &t, s_w);
-  if (threadIdx.x == d) s_base = below;
-  __syncthreads();
-  uint32_t carry = s_base;
-  uint32_t* row = hist + (size_t)d * nblocks;
-  for (uint32_t b0 = 0; b0 < nblocks; b0 += RS_THREADS) {
-    const uint32_t b = b0 + threadIdx.x;
-    const uint32_t v = b < nblocks ? row[b] : 0u;
-    const uint32_t p = block_excl_scan_u32(v, &t, s_w);
-    if (b < nblocks) row[b] = carry + p;
-    carry += t;
+  constexpr uint32_t PER = (uint32_t)(RS_MAX_BLOCKS / RS_THREADS);  // consecutive entries per thread
+  uint32_t* row = hist + (size_t)blockIdx.x * nblocks;
+  uint32_t v[PER], sum = 0, t;
+#pragma unroll
+  for (uint32_t j = 0; j < PER; ++j) {
+    const uint32_t b = threadIdx.x * PER + j;
+    v[j] = b < nblocks ? row[b] : 0u;
+    sum += v[j];
   }
-  if (d == 0) next_totals[threadIdx.x] = 0u;
+  uint32_t p = block_excl_scan_u32(sum, &t, s_w);
+#pragma unroll
+  for (uint32_t j = 0; j < PER; ++j) {
+    const uint32_t b = threadIdx.x * PER + j;
+    if (b < nblocks) row[b] = p;
+    p += v[j];
+  }
+  if (threadIdx.x == 0) totals[blockIdx.x] = t;
 }
 
-template <typename K, int RS_ITEMS>
+// totals null: hist is block-major counts ([nblocks][256], nblocks <=
+// RS_DIRECT); else digit-major prefixes with the digits' totals.
+template <typename K, int RS_ITEMS, bool VALS>
 __global__ __launch_bounds__(RS_THREADS) void rs_scatter_k(const K* kin, const uint32_t* vin,
                                                             K* kout, uint32_t* vout, int64_t n,
-                                                            int shift, int nbits,
-                                                            const uint32_t* off,
-                                                            uint32_t nblocks) {
+                                                            int shift, int nbits, const uint32_t* hist,
+                                                            const uint32_t* totals, uint32_t nblocks, uint32_t tpb) {
   constexpr int RS_TILE = RS_THREADS * RS_ITEMS;
   __shared__ uint32_t cnt[RS_WAVES][256];
-  const int lane = lane_id(), w = threadIdx.x >> 6;
-  for (int i = threadIdx.x; i < RS_WAVES * 256; i += RS_THREADS) (&cnt[0][0])[i] = 0;
-  __syncthreads();
-  const uint32_t dmask = (1u << nbits) - 1u;
-  const int64_t sub = (int64_t)blockIdx.x * RS_TILE + (int64_t)w * 64 * RS_ITEMS;
-  K key[RS_ITEMS];
-  uint32_t val[RS_ITEMS], rank[RS_ITEMS], dig[RS_ITEMS];
-#pragma unroll
-  for (int i = 0; i < RS_ITEMS; ++i) {
-    const int64_t idx = sub + (int64_t)i * 64 + lane;
-    const bool valid = idx < n;
-    key[i] = valid ? kin[idx] : (K)0;
-    val[i] = (valid && vin) ? vin[idx] : 0u;
-    const uint32_t d = (uint32_t)(key[i] >> shift) & dmask;
-    u64 peers = __ballot(valid);
-    for (int b = 0; b < nbits; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const u64 bal = __ballot(bit);
-      peers &= bit ? bal : ~bal;
-    }
-    if (!valid) peers = 0;
-    const uint32_t lt = __popcll(peers & lanemask_lt());
-    const uint32_t before = cnt[w][d];
-    wave_lds_sync();
-    rank[i] = before + lt;
-    dig[i] = valid ? d : 0xffffffffu;
-    if (valid && lt == 0) cnt[w][d] = before + (uint32_t)__popcll(peers);
-    wave_lds_sync();
-  }
-  __syncthreads();
   // the tile's keys in output order in LDS (digit, then wave, then rank), so
   // each digit's run goes out as consecutive stores
   __shared__ K sk[RS_TILE];
-  __shared__ uint32_t sv[RS_TILE];
-  __shared__ uint32_t toff[256], s_w[RS_WAVES];
-  {
-    uint32_t t = 0;
-    for (int ww = 0; ww < RS_WAVES; ++ww) t += cnt[ww][threadIdx.x];
-    uint32_t tot;
-    toff[threadIdx.x] = block_excl_scan_u32(t, &tot, s_w);
+  __shared__ uint32_t sv[VALS ? RS_TILE : 1];
+  __shared__ uint32_t toff[256], s_out[256], s_w[RS_WAVES];
+  const int lane = lane_id(), w = threadIdx.x >> 6;
+  const uint32_t dmask = (1u << nbits) - 1u;
+  uint32_t at, tot;  // where the block's next key of digit threadIdx.x goes
+  if (totals) {
+    at = block_excl_scan_u32(totals[threadIdx.x], &tot, s_w) + hist[(size_t)threadIdx.x * nblocks + blockIdx.x];
+  } else {
+    uint32_t all = 0, before = 0;
+#pragma unroll 8
+    for (uint32_t b = 0; b < nblocks; ++b) {
+      const uint32_t c = hist[(size_t)b * 256 + threadIdx.x];
+      all += c;
+      before += b < blockIdx.x ? c : 0u;
+    }
+    at = block_excl_scan_u32(all, &tot, s_w) + before;
   }
-  __syncthreads();
+  for (uint32_t tile = 0; tile < tpb; ++tile) {
+    const int64_t t0 = ((int64_t)blockIdx.x * tpb + tile) * RS_TILE;
+    if (t0 >= n) break;
+    for (int i = threadIdx.x; i < RS_WAVES * 256; i += RS_THREADS) (&cnt[0][0])[i] = 0;
+    const int64_t sub = t0 + (int64_t)w * 64 * RS_ITEMS;
+    K key[RS_ITEMS];
+    uint32_t val[RS_ITEMS], rank[RS_ITEMS];
 #pragma unroll
-  for (int i = 0; i < RS_ITEMS; ++i) {
-    const uint32_t d = dig[i];
-    if (d == 0xffffffffu) continue;
-    uint32_t pre = 0;
-    for (int ww = 0; ww < w; ++ww) pre += cnt[ww][d];
-    const uint32_t lp = toff[d] + pre + rank[i];
-    sk[lp] = key[i];
-    sv[lp] = val[i];
-  }
-  __syncthreads();
-  const int64_t t0 = (int64_t)blockIdx.x * RS_TILE;
-  const uint32_t tile_n = (uint32_t)min((int64_t)RS_TILE, n - t0);
-  for (uint32_t q = threadIdx.x; q < tile_n; q += RS_THREADS) {
-    const K k = sk[q];
-    const uint32_t d = (uint32_t)(k >> shift) & dmask;
-    const uint32_t pos = off[(size_t)d * nblocks + blockIdx.x] + (q - toff[d]);
-    kout[pos] = k;
-    if (vout) vout[pos] = sv[q];
+    for (int i = 0; i < RS_ITEMS; ++i) {
+      const int64_t idx = sub + (int64_t)i * 64 + lane;
+      key[i] = idx < n ? kin[idx] : (K)0;
+      val[i] = (VALS && idx < n) ? vin[idx] : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < RS_ITEMS; ++i) {
+      const bool valid = sub + (int64_t)i * 64 + lane < n;
+      const uint32_t d = (uint32_t)(key[i] >> shift) & dmask;
+      u64 peers = __ballot(valid);
+      for (int b = 0; b < nbits; ++b) {
+        const bool bit = (d >> b) & 1u;
+        const u64 bal = __ballot(bit);
+        peers &= bit ? bal : ~bal;
+      }
+      if (!valid) peers = 0;
+      const uint32_t lt = __popcll(peers & lanemask_lt());
+      const uint32_t before = cnt[w][d];
+      wave_lds_sync();
+      rank[i] = before + lt;
+      if (valid && lt == 0) cnt[w][d] = before + (uint32_t)__popcll(peers);
+      wave_lds_sync();
+    }
+    __syncthreads();
+    {
+      uint32_t t = 0;
+#pragma unroll
+      for (int ww = 0; ww < RS_WAVES; ++ww) {  // counts become the wave's first place in the digit's run
+        const uint32_t c = cnt[ww][threadIdx.x];
+        cnt[ww][threadIdx.x] = t;
+        t += c;
+      }
+      const uint32_t first = block_excl_scan_u32(t, &tot, s_w);
+      toff[threadIdx.x] = first;
+      s_out[threadIdx.x] = at - first;  // (modulo 2^32)
+      at += t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < RS_ITEMS; ++i) {
+      if (sub + (int64_t)i * 64 + lane >= n) continue;
+      const uint32_t d = (uint32_t)(key[i] >> shift) & dmask;
+      const uint32_t lp = toff[d] + cnt[w][d] + rank[i];
+      sk[lp] = key[i];
+      if (VALS) sv[lp] = val[i];
+    }
+    __syncthreads();
+    const uint32_t tile_n = (uint32_t)min((int64_t)RS_TILE, n - t0);
+#pragma unroll 4
+    for (uint32_t q = threadIdx.x; q < tile_n; q += RS_THREADS) {
+      const K k = sk[q];
+      const uint32_t pos = s_out[(uint32_t)(k >> shift) & dmask] + q;
+      kout[pos] = k;
+      if (VALS) vout[pos] = sv[q];
+    }
+    __syncthreads();
   }
 }
 
@@ -524,12 +570,35 @@ __global__ __launch_bounds__(SS_THREADS) void sort_small_k(K* keys, uint32_t* va
 }
 
 static int64_t rs_tile(int64_t n) { return (int64_t)RS_THREADS * (n < RS_SMALL_N ? RS_SMALL_ITEMS : 16); }
+// Tiles per workgroup and workgroups for n keys.
+static uint32_t rs_tpb(int64_t n) {
+  const int64_t tiles = (n + rs_tile(n) - 1) / rs_tile(n);
+  return (uint32_t)std::max<int64_t>(1, (tiles + RS_MAX_BLOCKS - 1) / RS_MAX_BLOCKS);
+}
+static uint32_t rs_blocks(int64_t n) {
+  const int64_t run = rs_tile(n) * rs_tpb(n);
+  return (uint32_t)std::max<int64_t>(1, (n + run - 1) / run);
+}
 
 size_t radix_temp_bytes(int64_t n) {
-  int64_t nb = (n + rs_tile(n) - 1) / rs_tile(n);
-  if (nb < 1) nb = 1;
-  size_t hist = (((size_t)nb * 256 * 4) + 255) & ~(size_t)255;
-  return hist + 2 * 256 * 4;  // + the digit totals of two consecutive passes
+  return (size_t)rs_blocks(n) * 256 * 4 + 256 * 4;  // the table and the digits' totals
+}
+
+template <typename K, int ITEMS>
+static hipError_t rs_pass(const K* ka, const uint32_t* va, K* kb, uint32_t* vb, int64_t n, int shift, int nbits,
+                          uint32_t* hist, hipStream_t s) {
+  const uint32_t nb = rs_blocks(n), tpb = rs_tpb(n), dmask = (1u << nbits) - 1u;
+  const bool direct = nb <= RS_DIRECT;
+  uint32_t* totals = hist + (size_t)nb * 256;
+  rs_hist_k<K, ITEMS><<<nb, RS_THREADS, 0, s>>>(ka, n, shift, dmask, hist, direct ? 1 : nb, direct ? 256 : 1, tpb);
+  if (!direct) rs_offsets_k<<<256, RS_THREADS, 0, s>>>(hist, nb, totals);
+  if (va)
+    rs_scatter_k<K, ITEMS, true><<<nb, RS_THREADS, 0, s>>>(ka, va, kb, vb, n, shift, nbits, hist,
+                                                           direct ? nullptr : totals, nb, tpb);
+  else
+    rs_scatter_k<K, ITEMS, false><<<nb, RS_THREADS, 0, s>>>(ka, nullptr, kb, nullptr, n, shift, nbits, hist,
+                                                            direct ? nullptr : totals, nb, tpb);
+  return hipGetLastError();
 }
 
 template <typename K>
@@ -541,35 +610,22 @@ static hipError_t radix_sort_t(K* keys, uint32_t* vals, K* keys_alt, uint32_t* v
     sort_small_k<K><<<1, SS_THREADS, 0, s>>>(keys, vals, (int)n, bits);
     return hipGetLastError();
   }
-  const bool small = n < RS_SMALL_N;
-  const uint32_t nb = (uint32_t)((n + rs_tile(n) - 1) / rs_tile(n));
-  uint32_t* hist = (uint32_t*)temp;
-  uint32_t* totals = (uint32_t*)((char*)temp + ((((size_t)nb * 256 * 4) + 255) & ~(size_t)255));
-  hipError_t e = hipMemsetAsync(totals, 0, 256 * 4, s);
-  if (e != hipSuccess) return e;
-  int pass = 0;
+  // even digits: as few passes as 8-bit digits need, each as narrow as they allow
+  const int passes = (bits + 7) / 8;
   K* ka = keys;
   K* kb = keys_alt;
   uint32_t* va = vals;
   uint32_t* vb = vals ? vals_alt : nullptr;
-  for (int shift = 0; shift < bits; shift += 8, ++pass) {
-    const int nbits = bits - shift < 8 ? bits - shift : 8;
-    uint32_t* tot = totals + 256 * (pass & 1);
-    uint32_t* tot_next = totals + 256 * ((pass + 1) & 1);
-    if (small)
-      rs_hist_k<K, RS_SMALL_ITEMS><<<nb, RS_THREADS, 0, s>>>(ka, n, shift, (1u << nbits) - 1u, hist, nb, tot);
-    else
-      rs_hist_k<K, 16><<<nb, RS_THREADS, 0, s>>>(ka, n, shift, (1u << nbits) - 1u, hist, nb, tot);
-    rs_offsets_k<<<256, RS_THREADS, 0, s>>>(hist, nb, tot, tot_next);
-    if (small)
-      rs_scatter_k<K, RS_SMALL_ITEMS><<<nb, RS_THREADS, 0, s>>>(ka, va, kb, vb, n, shift, nbits, hist, nb);
-    else
-      rs_scatter_k<K, 16><<<nb, RS_THREADS, 0, s>>>(ka, va, kb, vb, n, shift, nbits, hist, nb);
-    e = hipGetLastError();
+  for (int p = 0, shift = 0; p < passes; ++p) {
+    const int nbits = (bits - shift + passes - p - 1) / (passes - p);
+    const hipError_t e = n < RS_SMALL_N
+                             ? rs_pass<K, RS_SMALL_ITEMS>(ka, va, kb, vb, n, shift, nbits, (uint32_t*)temp, s)
+                             : rs_pass<K, 16>(ka, va, kb, vb, n, shift, nbits, (uint32_t*)temp, s);
     if (e != hipSuccess) return e;
-    K* tk = ka; ka = kb; kb = tk;
-    uint32_t* tv = va; va = vb; vb = tv;
+    std::swap(ka, kb);
+    std::swap(va, vb);
     *in_alt ^= 1;
+    shift += nbits;
   }
   return hipSuccess;
 }
