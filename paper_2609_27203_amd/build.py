@@ -25,7 +25,7 @@ LIB = os.path.join(HERE, "libxlh.so")
 CEILING_SRC, CEILING_LIB = "ceiling.hip", os.path.join(HERE, "libxlh_ceiling.so")
 ARCH = os.environ.get("XLH_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["kernels.hip", "frontier.hip", "wcoj.hip", "coding.hip", "engine.cpp", "frontend.cpp", "api.cpp"]
+SOURCES = ["kernels.hip", "frontier.hip", "wcoj.hip", "coding.hip", "rows.hip", "engine.cpp", "frontend.cpp", "api.cpp"]
 
 COMMON = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",

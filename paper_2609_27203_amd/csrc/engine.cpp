@@ -193,25 +193,104 @@ xl_status lex_perm(Context* c, uint32_t* const* cols, const uint8_t* types, int 
   return XL_OK;
 }
 
+// Rows sorted as packed keys (rows.hip): the key holds the first `by` columns,
+// a payload the one after them, if any.
+struct PackedRows {
+  Buf key, pay, key2, pay2;
+  k::RowPack r{};
+  int bits = 0;  // key bits
+  bool wide = false, has_pay = false;
+  void* skey() const { return key.p; }
+  uint32_t* spay() const { return has_pay ? pay.as<uint32_t>() : nullptr; }
+};
+
+// Key layout of columns whose images lie in [lo, hi]: as many leading columns
+// as 64 bits hold, at most one more as the payload.  keep (when positive) is a
+// number of leading columns that are known to be distinct: no more are packed
+// when the rest is one column.  False when the columns do not fit.
+bool row_layout(const uint8_t* types, int arity, const uint32_t* lo, const uint32_t* hi, int keep, PackedRows* x) {
+  int width[MAXC], by = 0, total = 0;
+  for (int j = 0; j < arity; ++j) width[j] = bitlen((uint64_t)hi[j] - lo[j]);
+  const int most = keep > 0 && keep == arity - 1 ? keep : arity;
+  while (by < most && total + width[by] <= 64) total += width[by++];
+  if (by < arity - 1) return false;
+  x->has_pay = by < arity;
+  x->bits = total;
+  x->wide = total > 32;
+  x->r.by = by;
+  for (int j = 0, at = total; j < arity; ++j) {
+    x->r.type[j] = types[j];
+    x->r.lo[j] = lo[j];
+    if (j < by) {
+      at -= width[j];
+      x->r.shift[j] = at >= (x->wide ? 64 : 32) ? 0 : at;  // (a constant column needs no bits)
+      x->r.mask[j] = width[j] >= 32 ? 0xffffffffu : (1u << width[j]) - 1u;
+    }
+  }
+  return true;
+}
+
+// Pack and sort n rows; the sorted keys and payloads end in x->key, x->pay.
+// free_input (optional) runs once the columns have been read.
+template <typename F>
+xl_status sort_packed(Context* c, PackedRows* x, int64_t n, F free_input) {
+  const size_t kb = x->wide ? 8 : 4;
+  Buf tmp;
+  XL_TRY(dalloc(c, (size_t)n * kb, &x->key, "sort keys"));
+  if (x->has_pay) XL_TRY(dalloc(c, (size_t)n * 4, &x->pay, "sort payload"));
+  HIP_TRY(c, k::pack_rows(x->r, n, x->key.p, x->wide, x->spay(), c->stream));
+  free_input();
+  XL_TRY(dalloc(c, (size_t)n * kb, &x->key2, "sort keys"));
+  if (x->has_pay) XL_TRY(dalloc(c, (size_t)n * 4, &x->pay2, "sort payload"));
+  XL_TRY(dalloc(c, k::radix_temp_bytes(n), &tmp, "sort scratch"));
+  int alt = 0;
+  uint32_t* pay2 = x->has_pay ? x->pay2.as<uint32_t>() : nullptr;
+  if (x->wide)
+    HIP_TRY(c, k::radix_sort_u64(x->key.as<u64>(), x->spay(), x->key2.as<u64>(), pay2, n, x->bits, tmp.p, c->stream,
+                                 &alt));
+  else
+    HIP_TRY(c, k::radix_sort_u32(x->key.as<uint32_t>(), x->spay(), x->key2.as<uint32_t>(), pay2, n, x->bits, tmp.p,
+                                 c->stream, &alt));
+  if (alt) {
+    std::swap(x->key.p, x->key2.p);
+    std::swap(x->pay.p, x->pay2.p);
+  }
+  x->key2.reset();
+  x->pay2.reset();
+  return XL_OK;
+}
+
+// Least and greatest image of every column (n > 0 rows).
+xl_status image_bounds(Context* c, const uint32_t* const* cols, const uint8_t* types, int arity, int64_t n,
+                       uint32_t* lo, uint32_t* hi) {
+  Buf b;
+  XL_TRY(dalloc(c, 8 * MAXC, &b, "bounds"));
+  k::RowPack r{};
+  for (int j = 0; j < arity; ++j) {
+    r.col[j] = cols[j];
+    r.type[j] = types[j];
+  }
+  HIP_TRY(c, k::col_bounds(r, arity, n, b.as<uint32_t>(), c->stream));
+  uint32_t out[2 * MAXC];
+  XL_TRY(ctl_read(c, b.p, sizeof(out), out));
+  for (int j = 0; j < arity; ++j) {
+    lo[j] = ~out[2 * j];
+    hi[j] = out[2 * j + 1];
+  }
+  return XL_OK;
+}
+
+inline int32_t image_i32(uint32_t image) { return (int32_t)(image ^ 0x80000000u); }
+
 xl_status compute_bounds(Context* c, Relation* r) {
   if (r->nrows == 0) return XL_OK;
-  Buf mm;
-  XL_TRY(dalloc(c, 8 * MAXC, &mm, "bounds"));
-  int32_t init[2 * MAXC];
-  for (int j = 0; j < MAXC; ++j) {
-    init[2 * j] = INT32_MAX;
-    init[2 * j + 1] = INT32_MIN;
-  }
-  HIP_TRY(c, hipMemcpyAsync(mm.p, init, sizeof(init), hipMemcpyHostToDevice, c->stream));
+  uint32_t lo[MAXC], hi[MAXC];
+  XL_TRY(image_bounds(c, r->col, r->types, r->arity, r->nrows, lo, hi));
   for (int j = 0; j < r->arity; ++j)
-    if (r->types[j] == T_I32)
-      HIP_TRY(c, k::minmax_i32((const int32_t*)r->col[j], r->nrows, mm.as<int32_t>() + 2 * j, c->stream));
-  int32_t out[2 * MAXC];
-  XL_TRY(ctl_read(c, mm.p, sizeof(out), out));
-  for (int j = 0; j < r->arity; ++j) {
-    r->lo[j] = out[2 * j];
-    r->hi[j] = out[2 * j + 1];
-  }
+    if (r->types[j] == T_I32) {
+      r->lo[j] = image_i32(lo[j]);
+      r->hi[j] = image_i32(hi[j]);
+    }
   return XL_OK;
 }
 
@@ -416,6 +495,7 @@ void relation_free_storage(Relation* r) {
   }
   r->nrows = 0;
   r->sorted = false;
+  r->key_cols = 0;
   r->generation = ++r->ctx->generations;  // cached indexes of the old rows no longer match
   r->ctx->icache_drop(r, true);
 }
@@ -426,6 +506,103 @@ xl_status relation_clear(Relation* r) {
 }
 
 // ================================================================== load / read
+namespace {
+
+// The distinct rows of the loaded columns in canonical order, by one sort of
+// packed keys.  *done stays false when the columns do not fit a key and a
+// payload, when the workspace does not hold the sort, or when more rows than
+// a run may hold agree in all columns but the last (that one is then the
+// payload, ordered run by run): the caller sorts column by column instead.
+// Raw columns released by then are all written again, in another row order.
+xl_status load_packed(Context* c, const Relation* r, const uint32_t* const* rc, Buf* raw, int64_t n,
+                      const uint32_t* lo, const uint32_t* hi, Buf* fin, int64_t* m, bool* done) {
+  *done = false;
+  PackedRows x;
+  if (!row_layout(r->types, r->arity, lo, hi, 0, &x)) return XL_OK;
+  for (int j = 0; j < r->arity; ++j) {
+    x.r.col[j] = rc[j];
+    x.r.ltype[j] = r->types[j] == T_F32 ? XL_F32 : XL_I32;  // images stay as they are
+  }
+  bool freed = false;
+  const xl_status st = sort_packed(c, &x, n, [&]() {
+    for (int j = 0; j < r->arity; ++j) {
+      freed = freed || raw[j].p;
+      raw[j].reset();
+    }
+  });
+  auto give_back = [&]() -> xl_status {  // every column from the keys (all in one row order)
+    for (int j = 0; j < r->arity; ++j) {
+      XL_TRY(dalloc(c, (size_t)n * 4, &raw[j], "loaded column"));
+      x.r.dst[j] = raw[j].p;
+    }
+    HIP_TRY(c, k::unpack_rows(x.r, x.skey(), x.wide, x.spay(), n, nullptr, c->stream));
+    return XL_OK;
+  };
+  if (st == XL_RESOURCE_EXHAUSTED) {
+    if (!freed) return XL_OK;
+    x.key2.reset();
+    x.pay2.reset();
+    return give_back();
+  }
+  if (st != XL_OK) return st;
+  const int64_t nt = k::row_tiles(n);
+  Buf cnt, off, tmp, tot;
+  XL_TRY(dalloc(c, (size_t)nt * 4, &cnt, "dedup counts"));
+  XL_TRY(dalloc(c, (size_t)nt * 4, &off, "dedup offsets"));
+  XL_TRY(dalloc(c, k::scan_temp_bytes(nt), &tmp, "scan scratch"));
+  XL_TRY(dalloc(c, 8, &tot, "count"));
+  if (x.has_pay) {
+    HIP_TRY(c, hipMemsetAsync(tot.p, 0, 8, c->stream));
+    HIP_TRY(c, k::sort_runs(x.skey(), x.wide, x.spay(), n, tot.as<uint32_t>() + 1, c->stream));
+  }
+  HIP_TRY(c, k::count_rows(x.skey(), x.wide, x.spay(), n, cnt.as<uint32_t>(), c->stream));
+  HIP_TRY(c, k::scan_exclusive_u32(cnt.as<uint32_t>(), off.as<uint32_t>(), nt, tot.as<uint32_t>(), tmp.p, c->stream));
+  uint32_t t[2] = {0, 0};
+  XL_TRY(ctl_read(c, tot.p, x.has_pay ? 8 : 4, t));
+  if (t[1]) return give_back();
+  *m = t[0];
+  for (int j = 0; j < r->arity; ++j) {
+    XL_TRY(dalloc(c, (size_t)*m * 4, &fin[j], "relation column"));
+    x.r.dst[j] = fin[j].p;
+  }
+  HIP_TRY(c, k::unpack_rows(x.r, x.skey(), x.wide, x.spay(), n, off.as<uint32_t>(), c->stream));
+  *done = true;
+  return XL_OK;
+}
+
+// The same by successive stable sorts of single columns (any columns).
+xl_status load_by_columns(Context* c, const Relation* r, uint32_t* const* rc, Buf* raw, int64_t n, Buf* fin,
+                          int64_t* m) {
+  Buf perm;
+  XL_TRY(lex_perm(c, rc, r->types, r->arity, n, &perm));
+  Buf sorted[MAXC];
+  const uint32_t* sc[MAXC] = {};
+  for (int j = 0; j < r->arity; ++j) {
+    XL_TRY(dalloc(c, (size_t)n * 4, &sorted[j], "sorted column"));
+    HIP_TRY(c, k::gather_u32(rc[j], perm.as<uint32_t>(), sorted[j].as<uint32_t>(), n, c->stream));
+    sc[j] = sorted[j].as<uint32_t>();
+    raw[j].reset();
+  }
+  Buf flag, pos, tmp, tot;
+  XL_TRY(dalloc(c, (size_t)n * 4, &flag, "dedup flags"));
+  XL_TRY(dalloc(c, (size_t)n * 4, &pos, "dedup positions"));
+  XL_TRY(dalloc(c, k::scan_temp_bytes(n), &tmp, "scan scratch"));
+  XL_TRY(dalloc(c, 8, &tot, "count"));
+  HIP_TRY(c, k::row_change_flags(sc, r->arity, n, flag.as<uint32_t>(), c->stream));
+  HIP_TRY(c, k::scan_exclusive_u32(flag.as<uint32_t>(), pos.as<uint32_t>(), n, tot.as<uint32_t>(), tmp.p,
+                                   c->stream));
+  uint32_t mm = 0;
+  XL_TRY(ctl_read(c, tot.p, 4, &mm));
+  *m = mm;
+  for (int j = 0; j < r->arity; ++j) {
+    XL_TRY(dalloc(c, (size_t)*m * 4, &fin[j], "relation column"));
+    HIP_TRY(c, k::compact_u32(sc[j], flag.as<uint32_t>(), pos.as<uint32_t>(), fin[j].as<uint32_t>(), n, c->stream));
+  }
+  return XL_OK;
+}
+
+}  // namespace
+
 xl_status relation_load(Relation* r, const void* const* cols, int64_t n, int on_device) {
   Context* c = r->ctx;
   if (c->device < 0) return c->fail(XL_INVALID_ARGUMENT, "planning-only context cannot hold data");
@@ -439,60 +616,80 @@ xl_status relation_load(Relation* r, const void* const* cols, int64_t n, int on_
   }
   Buf raw[MAXC];
   uint32_t* img[MAXC] = {};
+  const uint32_t* rc[MAXC] = {};  // columns as images; the caller's own where it is device memory that needs no coding
   for (int j = 0; j < r->arity; ++j) {
+    const bool plain = r->ltypes[j] == XL_I32 || r->ltypes[j] == XL_F32;
+    if (plain && on_device && (uintptr_t)cols[j] % 4 == 0) {
+      rc[j] = (const uint32_t*)cols[j];
+      continue;
+    }
     XL_TRY(dalloc(c, (size_t)n * 4, &raw[j], "loaded column"));
-    img[j] = raw[j].as<uint32_t>();
-    if (r->ltypes[j] == XL_I32 || r->ltypes[j] == XL_F32)
+    rc[j] = img[j] = raw[j].as<uint32_t>();
+    if (plain)
       HIP_TRY(c, hipMemcpyAsync(raw[j].p, cols[j], (size_t)n * 4,
                                 on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
   }
   XL_TRY(encode_columns(c, r, cols, n, on_device, img));
-  int64_t m = n;
+  // sets: sort the rows, keep those that differ from their predecessor
   Buf fin[MAXC];
-  if (n == 1) {
-    for (int j = 0; j < r->arity; ++j) std::swap(fin[j].p, raw[j].p), fin[j].c = c;
+  int64_t m = 0;
+  uint32_t lo[MAXC], hi[MAXC];
+  XL_TRY(image_bounds(c, rc, r->types, r->arity, n, lo, hi));
+  bool done = n == 1;
+  if (done) {
+    m = 1;
+    for (int j = 0; j < r->arity; ++j) {
+      XL_TRY(dalloc(c, 4, &fin[j], "relation column"));
+      HIP_TRY(c, hipMemcpyAsync(fin[j].p, rc[j], 4, hipMemcpyDeviceToDevice, c->stream));
+    }
   } else {
-    // sets: sort rows, flag rows that differ from their predecessor, compact
-    uint32_t* rc[MAXC] = {};
-    for (int j = 0; j < r->arity; ++j) rc[j] = raw[j].as<uint32_t>();
-    Buf perm;
-    XL_TRY(lex_perm(c, rc, r->types, r->arity, n, &perm));
-    Buf sorted[MAXC];
-    const uint32_t* sc[MAXC] = {};
+    XL_TRY(load_packed(c, r, rc, raw, n, lo, hi, fin, &m, &done));
+  }
+  if (!done) {
+    uint32_t* lc[MAXC] = {};
     for (int j = 0; j < r->arity; ++j) {
-      XL_TRY(dalloc(c, (size_t)n * 4, &sorted[j], "sorted column"));
-      HIP_TRY(c, k::gather_u32(rc[j], perm.as<uint32_t>(), sorted[j].as<uint32_t>(), n, c->stream));
-      sc[j] = sorted[j].as<uint32_t>();
-      raw[j].reset();
+      if (!raw[j].p) {  // (not read yet, or handed back by the packed sort)
+        XL_TRY(dalloc(c, (size_t)n * 4, &raw[j], "loaded column"));
+        HIP_TRY(c, hipMemcpyAsync(raw[j].p, cols[j], (size_t)n * 4, hipMemcpyDeviceToDevice, c->stream));
+      }
+      lc[j] = raw[j].as<uint32_t>();
     }
-    Buf flag, pos, tmp, tot;
-    XL_TRY(dalloc(c, (size_t)n * 4, &flag, "dedup flags"));
-    XL_TRY(dalloc(c, (size_t)n * 4, &pos, "dedup positions"));
-    XL_TRY(dalloc(c, k::scan_temp_bytes(n), &tmp, "scan scratch"));
-    XL_TRY(dalloc(c, 8, &tot, "count"));
-    HIP_TRY(c, k::row_change_flags(sc, r->arity, n, flag.as<uint32_t>(), c->stream));
-    HIP_TRY(c, k::scan_exclusive_u32(flag.as<uint32_t>(), pos.as<uint32_t>(), n, tot.as<uint32_t>(),
-                                     tmp.p, c->stream));
-    uint32_t mm = 0;
-    XL_TRY(ctl_read(c, tot.p, 4, &mm));
-    m = mm;
-    for (int j = 0; j < r->arity; ++j) {
-      XL_TRY(dalloc(c, (size_t)m * 4, &fin[j], "relation column"));
-      HIP_TRY(c, k::compact_u32(sc[j], flag.as<uint32_t>(), pos.as<uint32_t>(), fin[j].as<uint32_t>(),
-                                n, c->stream));
-    }
+    XL_TRY(load_by_columns(c, r, lc, raw, n, fin, &m));
   }
   if (r->max_rows > 0 && m > r->max_rows)
     return c->fail(XL_CAPACITY_EXCEEDED, "relation " + r->name + " holds at most " +
                                              std::to_string(r->max_rows) + " rows, load has " +
                                              std::to_string(m));
   relation_free_storage(r);
-  for (int j = 0; j < r->arity; ++j) r->col[j] = (uint32_t*)fin[j].keep();
+  for (int j = 0; j < r->arity; ++j) {
+    r->col[j] = (uint32_t*)fin[j].keep();
+    if (r->types[j] == T_I32) {
+      r->lo[j] = image_i32(lo[j]);
+      r->hi[j] = image_i32(hi[j]);
+    }
+  }
   r->nrows = m;
   r->sorted = true;  // the deduplication above leaves the rows in lexicographic order
-  XL_TRY(compute_bounds(c, r));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return XL_OK;
+}
+
+// Sorts the rows of a relation whose leading key_cols columns are distinct and
+// bounded as packed keys; false when they do not fit, or the workspace does
+// not hold the sort.
+static bool sorted_for_read(Context* c, const Relation* r, int64_t n, PackedRows* x) {
+  uint32_t lo[MAXC], hi[MAXC];
+  for (int j = 0; j < r->arity; ++j) {
+    const bool i32 = r->types[j] == T_I32;
+    lo[j] = i32 ? (uint32_t)r->lo[j] ^ 0x80000000u : 0u;
+    hi[j] = i32 ? (uint32_t)r->hi[j] ^ 0x80000000u : 0xffffffffu;
+    x->r.col[j] = r->col[j];
+  }
+  if (r->key_cols == 0 || !row_layout(r->types, r->arity, lo, hi, r->key_cols, x)) return false;
+  if (x->has_pay && x->r.by != r->key_cols) return false;
+  if (sort_packed(c, x, n, []() {}) == XL_OK) return true;
+  for (Buf* b : {&x->key, &x->pay, &x->key2, &x->pay2}) b->reset();
+  return false;
 }
 
 xl_status relation_read(const Relation* r, void* const* cols, int64_t cap, int64_t* out_rows,
@@ -518,15 +715,17 @@ xl_status relation_read(const Relation* r, void* const* cols, int64_t cap, int64
       HIP_TRY(c, hipStreamSynchronize(c->stream));
       return XL_OK;
     };
+    // the workspace a read asks for is the column sort's, whatever route it
+    // takes (host bookkeeping only)
+    {
+      LexScratch reserve;
+      XL_TRY(lex_scratch(c, n, &reserve));
+    }
     Buf stage, img;
     if (r->sorted) {
       // rows already in canonical order (a load, a bitmap, a dense array or a
       // triangle join wrote them so): no sort, one pass over the columns
       // (reading the 129 M-row R-MAT closure to the device: 16.0 -> 0.4 ms).
-      // The workspace a read asks for does not depend on the row order: the
-      // sort's scratch is reserved (host bookkeeping only) here as well.
-      LexScratch reserve;
-      XL_TRY(lex_scratch(c, n, &reserve));
       k::ReadCols rc{};
       int nc = 0;
       for (int j = 0; j < r->arity; ++j) {
@@ -545,6 +744,22 @@ xl_status relation_read(const Relation* r, void* const* cols, int64_t cap, int64
           continue;
         }
         HIP_TRY(c, k::decode_column(r->col[j], n, r->ltypes[j], c->dict[r->ltypes[j]], stage.p, c->stream));
+        XL_TRY(copy_out(j, stage.p));
+      }
+    } else if (PackedRows x; sorted_for_read(c, r, n, &x)) {
+      // the rows from their sorted keys: the columns written directly in one
+      // launch, then the staged ones
+      for (int j = 0; j < r->arity; ++j) {
+        x.r.ltype[j] = r->ltypes[j];
+        x.r.dict[j] = c->dict[r->ltypes[j]];
+        x.r.dst[j] = direct(j) ? cols[j] : nullptr;
+      }
+      HIP_TRY(c, k::unpack_rows(x.r, x.skey(), x.wide, x.spay(), n, nullptr, c->stream));
+      for (int j = 0; j < r->arity; ++j) {
+        if (direct(j)) continue;
+        if (!stage.p) XL_TRY(dalloc(c, (size_t)n * 8, &stage, "readout staging"));
+        for (int q = 0; q < r->arity; ++q) x.r.dst[q] = q == j ? stage.p : nullptr;
+        HIP_TRY(c, k::unpack_rows(x.r, x.skey(), x.wide, x.spay(), n, nullptr, c->stream));
         XL_TRY(copy_out(j, stage.p));
       }
     } else {
@@ -3476,19 +3691,10 @@ struct Runner {
       r->hi[j] = (int32_t)h->dom_hi[j];
     }
     if (h->nkey < r->arity && r->types[h->nkey] == T_I32 && !h->vbounds) {
-      Buf mm;
-      XL_TRY(dalloc(c, 8, &mm, "bounds"));
-      if (r->nrows <= BOUNDS_ONE_MAX) {
-        HIP_TRY(c, k::bounds_one((const int32_t*)r->col[h->nkey], nullptr, r->nrows, mm.as<int32_t>(), c->stream));
-      } else {
-        HIP_TRY(c, hipMemsetD32Async(mm.as<int32_t>(), INT32_MAX, 1, c->stream));
-        HIP_TRY(c, hipMemsetD32Async(mm.as<int32_t>() + 1, INT32_MIN, 1, c->stream));
-        HIP_TRY(c, k::minmax_i32((const int32_t*)r->col[h->nkey], r->nrows, mm.as<int32_t>(), c->stream));
-      }
-      int32_t out[2];
-      XL_TRY(ctl_read(c, mm.p, 8, out));
-      r->lo[h->nkey] = out[0];
-      r->hi[h->nkey] = out[1];
+      uint32_t lo, hi;
+      XL_TRY(image_bounds(c, &r->col[h->nkey], &r->types[h->nkey], 1, r->nrows, &lo, &hi));
+      r->lo[h->nkey] = image_i32(lo);
+      r->hi[h->nkey] = image_i32(hi);
     }
     return XL_OK;
   }
@@ -3640,6 +3846,7 @@ struct Runner {
       relation_free_storage(r);
       for (int j = 0; j < h->nkey; ++j) r->col[j] = (uint32_t*)h->rows[j].keep();
       r->nrows = h->nrows;
+      r->key_cols = h->nkey;
     } else {
       Buf out[3];
       const int64_t n = h->keys;
@@ -3657,6 +3864,7 @@ struct Runner {
       relation_free_storage(r);
       for (int j = 0; j <= h->nkey; ++j) r->col[j] = (uint32_t*)out[j].keep();
       r->nrows = n;
+      r->key_cols = h->nkey;
     }
     return XL_OK;
   }

@@ -68,6 +68,7 @@ struct Relation {
   int64_t nrows = 0;
   int32_t lo[MAXC] = {}, hi[MAXC] = {};  // bounds of i32 columns when nrows > 0
   bool sorted = false;  // rows in ascending lexicographic order (loads, bitmaps, dense arrays, triangle joins)
+  int key_cols = 0;     // unsorted rows: leading columns no two rows agree in (0: not known)
   uint64_t generation = 0;  // new value (unique in the context) whenever the rows change
 };
 

@@ -42,9 +42,6 @@ hipError_t keys_perm(const uint32_t* col, int32_t lo, int64_t n, uint32_t* key, 
 // Order-preserving u32 image of a column: i32 signed order, f32 totalOrder.
 hipError_t ordered_key(const uint32_t* col, int type, const uint32_t* perm, uint32_t* out,
                        int64_t n, hipStream_t s);
-// out[0] = min, out[1] = max over an i32 column (out must be initialised by caller
-// to {INT32_MAX, INT32_MIN}).
-hipError_t minmax_i32(const int32_t* col, int64_t n, int32_t* out, hipStream_t s);
 hipError_t bounds_one(const int32_t* col, const uint32_t* count, int64_t cap, int32_t* out, hipStream_t s);
 // key[i] = col[i] - lo as unsigned.
 hipError_t sub_lo(const uint32_t* col, int32_t lo, uint32_t* out, int64_t n, hipStream_t s);
@@ -296,6 +293,35 @@ struct ReadCols {
   int ltype[MAXC];
 };
 hipError_t read_columns(const ReadCols& r, int ncols, int64_t n, hipStream_t s);
+
+// ---- rows as sort keys (rows.hip) ----
+// Columns j < by are packed into the key: (image - lo[j]) << shift[j], bits
+// mask[j] wide; column by (if any) is the payload, as its image.  dst[j] (null:
+// skipped) receives column j decoded by ltype[j] (dict[j]: its dictionary).
+struct RowPack {
+  const uint32_t* col[MAXC];
+  uint8_t type[MAXC];  // ValType of the stored column
+  uint32_t lo[MAXC];   // least image
+  uint32_t mask[MAXC];
+  int shift[MAXC];
+  int by;
+  void* dst[MAXC];
+  const u64* dict[MAXC];
+  int ltype[MAXC];
+};
+// out[2j] = complement of the least image of column j, out[2j + 1] = its
+// greatest image (2 * MAXC words, cleared by the call).
+hipError_t col_bounds(const RowPack& r, int ncols, int64_t n, uint32_t* out, hipStream_t s);
+hipError_t pack_rows(const RowPack& r, int64_t n, void* key, bool wide, uint32_t* pay, hipStream_t s);
+// Payload order within runs of equal keys; *flag |= 1 when a run is too long.
+hipError_t sort_runs(const void* key, bool wide, uint32_t* pay, int64_t n, uint32_t* flag, hipStream_t s);
+// Distinct rows per tile of the sorted rows (row_tiles(n) counts), and the
+// rows written out: distinct ones at the tiles' offsets off, or (off null)
+// every row.
+int64_t row_tiles(int64_t n);
+hipError_t count_rows(const void* key, bool wide, const uint32_t* pay, int64_t n, uint32_t* cnt, hipStream_t s);
+hipError_t unpack_rows(const RowPack& r, const void* key, bool wide, const uint32_t* pay, int64_t n,
+                       const uint32_t* off, hipStream_t s);
 
 }  // namespace k
 }  // namespace xlh

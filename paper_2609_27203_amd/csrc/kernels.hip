@@ -733,38 +733,6 @@ hipError_t ordered_key(const uint32_t* col, int type, const uint32_t* perm, uint
   return hipGetLastError();
 }
 
-__global__ void minmax_k(const int32_t* col, int64_t n, int32_t* out) {
-  int32_t lo = INT32_MAX, hi = INT32_MIN;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    lo = min(lo, col[i]);
-    hi = max(hi, col[i]);
-  }
-  for (int d = 32; d > 0; d >>= 1) {
-    lo = min(lo, __shfl_xor(lo, d, 64));
-    hi = max(hi, __shfl_xor(hi, d, 64));
-  }
-  // one atomic pair per workgroup: same-address atomics serialize
-  __shared__ int32_t s_lo[4], s_hi[4];
-  if (lane_id() == 0) {
-    s_lo[threadIdx.x >> 6] = lo;
-    s_hi[threadIdx.x >> 6] = hi;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
-      lo = min(lo, s_lo[w]);
-      hi = max(hi, s_hi[w]);
-    }
-    atomicMin(&out[0], lo);
-    atomicMax(&out[1], hi);
-  }
-}
-hipError_t minmax_i32(const int32_t* col, int64_t n, int32_t* out, hipStream_t s) {
-  minmax_k<<<grid_for(n, 256, 2048), 256, 0, s>>>(col, n, out);
-  return hipGetLastError();
-}
-
 // out = {min, max} of col[0, m), m = *count (at most cap) or cap when count
 // is null; {INT32_MAX, INT32_MIN} for no rows.  One workgroup, no
 // initialized output: for short columns (a few tens of thousands of rows).
