@@ -81,6 +81,18 @@ __device__ __forceinline__ u64 atomic_load_agent(const u64* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Counter updates of one workgroup, by one of its wavefronts (the arguments
+// uniform): one atomic instruction whose lanes hold neighbouring counters.  A
+// launch's counters share a cache line, and the transactions on one line are
+// served one after another (about 12 ns each across the XCDs), so a workgroup
+// that updates three counters should cost one of them, not three.  Lane
+// CNT_APPENDED receives the counter's value before.
+__device__ __forceinline__ u64 wave_counters_add(u64* counters, u64 appended, u64 inserted, u64 cands) {
+  const int lane = lane_id();
+  const u64 v = lane == CNT_APPENDED ? appended : lane == CNT_INSERTED ? inserted : lane == CNT_CANDIDATES ? cands : 0;
+  return v ? atomicAdd(&counters[lane], v) : 0;
+}
+
 static inline unsigned grid_for(int64_t n, int per_block, int cap = 1 << 20) {
   int64_t g = (n + per_block - 1) / per_block;
   if (g < 1) g = 1;

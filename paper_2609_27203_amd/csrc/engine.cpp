@@ -824,6 +824,8 @@ struct HeadRun {
   int fold = k::FOLD_NONE;
   bool is_set = false, is_minmax = false, is_sortagg = false;
   int nkey = 1;
+  bool once = false;  // head of a non-recursive stratum: no delta is kept
+  bool lean = false;  // the same for dense values (unless the receipt counts listed slots)
   KeyPack kp{};
   int bits0 = 1;      // width of the first packed key component
   double domain = 0;  // number of possible keys
@@ -1306,7 +1308,9 @@ struct Runner {
     if (hr->is_minmax && h->nrows > 0) src.push_back({h, 0});  // loaded rows
     hr->dv = true;
     hr->dmap_n = r0;
-    hr->range1 = (r1 + 31) / 32 * 32;  // rank rows start on word boundaries
+    // rank rows start on word boundaries; a head without a second key has one
+    // slot per rank
+    hr->range1 = hr->nkey == 2 ? (r1 + 31) / 32 * 32 : 1;
     hr->dict_src = src;
   }
 
@@ -1354,6 +1358,8 @@ struct Runner {
       hr->is_set = hr->agg == Agg::NONE;
       hr->is_minmax = hr->agg == Agg::MIN || hr->agg == Agg::MAX;
       hr->is_sortagg = !hr->is_set && !hr->is_minmax;
+      hr->once = !s.recursive;
+      hr->lean = hr->once && !c->profile;
       switch (hr->agg) {
         case Agg::COUNT: hr->fold = k::FOLD_COUNT; break;
         case Agg::SUM: hr->fold = k::FOLD_SUM; break;
@@ -1471,8 +1477,10 @@ struct Runner {
     const size_t bytes = (size_t)(total_bits / 8);
     XL_TRY(dalloc(c, bytes, &h->bits, "dense key bitmap"));
     HIP_TRY(c, k::fill_bytes(h->bits.p, 0, bytes, c->stream));
-    XL_TRY(dalloc(c, bytes, &h->dbits, "dense delta bitmap"));
-    HIP_TRY(c, k::fill_bytes(h->dbits.p, 0, bytes, c->stream));
+    if (!h->once) {
+      XL_TRY(dalloc(c, bytes, &h->dbits, "dense delta bitmap"));
+      HIP_TRY(c, k::fill_bytes(h->dbits.p, 0, bytes, c->stream));
+    }
     // the row list only holds loaded rows (the seed scans them); derived
     // tuples live in the bitmap and each round's delta in dbits
     h->rows_cap = std::max<int64_t>(h->preloaded, 1);
@@ -1567,10 +1575,12 @@ struct Runner {
     const size_t ns = h->ds ? (size_t)h->nrank_d * (size_t)h->range1 : (size_t)slots, nw = (ns + 31) / 32;
     XL_TRY(dalloc(c, ns * 4, &h->dvals, "dense values"));
     XL_TRY(dalloc(c, nw * 4, &h->dpres, "dense presence bits"));
-    XL_TRY(dalloc(c, nw * 4, &h->dchg, "dense delta bits"));
     HIP_TRY(c, k::fill_bytes(h->dvals.p, 0xff, ns * 4, c->stream));
     HIP_TRY(c, k::fill_bytes(h->dpres.p, 0, nw * 4, c->stream));
-    HIP_TRY(c, k::fill_bytes(h->dchg.p, 0, nw * 4, c->stream));
+    if (!h->lean) {
+      XL_TRY(dalloc(c, nw * 4, &h->dchg, "dense delta bits"));
+      HIP_TRY(c, k::fill_bytes(h->dchg.p, 0, nw * 4, c->stream));
+    }
     if (h->tiled) XL_TRY(dalloc(c, (size_t)(n0 + 1) * 4, &h->roff, "delta rows per rank"));
     if (h->ds) {
       // target-major delta slots with whole words per target: y * nrank_d + rank
@@ -1583,7 +1593,7 @@ struct Runner {
       HIP_TRY(c, k::fill_bytes(h->dcur_pres.p, 0, nwd * 4, c->stream));
       HIP_TRY(c, k::fill_bytes(h->dnext_pres.p, 0, nwd * 4, c->stream));
       HIP_TRY(c, k::fill_bytes(h->dchg.p, 0, nwd * 4, c->stream));
-    } else {
+    } else if (!h->lean) {
       XL_TRY(dalloc(c, ns * 4, &h->didx, "delta slot list"));
     }
     h->keys = 0;
@@ -3374,7 +3384,7 @@ struct Runner {
           a.emit.dpres = h->dpres.as<uint32_t>();
           a.emit.dchg = h->dchg.as<uint32_t>();
           a.emit.is_max = h->agg == Agg::MAX;
-          a.emit.delta_idx = h->didx.as<uint32_t>() + h->didx_n;
+          a.emit.delta_idx = h->lean ? nullptr : h->didx.as<uint32_t>() + h->didx_n;
         } else if (h->dense) {  // bitmap and delta bitmap cover the whole domain
           HIP_TRY(c, hipMemsetAsync(c->dcounters, 0, 8 * CNT_N, c->stream));
           a.emit.limit = ~0ull;
@@ -3487,6 +3497,10 @@ struct Runner {
     if (h->gathered && h->gather_ready) {  // a gathered round wrote the next delta rows
       h->gcur ^= 1;
       *delta = h->fnew;
+      return XL_OK;
+    }
+    if (h->once && (h->dense || h->is_minmax)) {  // no round follows
+      *delta = h->dense ? h->round_new : h->didx_n;
       return XL_OK;
     }
     if (h->dense) {

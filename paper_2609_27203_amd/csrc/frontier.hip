@@ -347,16 +347,26 @@ hipError_t frontier_round(const FrontierArgs& a, hipStream_t s) {
 // Resident form (see FrontierArgs): the rounds of one first key x depend only
 // on x's own row and the fixed index, so a workgroup runs them back to back
 // with the row, the delta and the next row in LDS and no launch, host read or
-// HBM round trip in between.
-__global__ __launch_bounds__(FR_THREADS) void frontier_resident_k(FrontierArgs a) {
+// HBM round trip in between.  The per-round counts stay in LDS until the
+// workgroup has no more keys: an atomic per key and round on their one cache
+// line, waited for at the next barrier, cost the R-MAT closure 678 -> 643 us
+// and a 1,000-node uniform one 105 -> 78.  Drawing the next key's ticket while
+// the current key runs was slower (700 us): the first barrier waits for it.
+// Six wavefronts per SIMD are asked for: the LDS holds six workgroups, and one
+// register more than 80 took them down to five (738 us).
+constexpr uint32_t FR_ROUNDS = 64;  // rounds counted in LDS (one per lane of the flush)
+__global__ __launch_bounds__(FR_THREADS, 6) void frontier_resident_k(FrontierArgs a) {
   extern __shared__ uint32_t lds[];
   uint32_t* old_row = lds;
   uint32_t* new_row = lds + a.row_words;
   uint32_t* f_row = lds + 2 * a.row_words;
   __shared__ FrontierShared L;
+  __shared__ u64 s_round[FR_ROUNDS];  // new tuples of the workgroup's keys by round
   const int lane = lane_id(), w = threadIdx.x >> 6;
   const uint32_t W = a.row_words;
   u64 cands = 0, news = 0;
+  uint32_t max_round = 0;
+  for (uint32_t i = threadIdx.x; i < FR_ROUNDS; i += FR_THREADS) s_round[i] = 0;
   for (;;) {
     if (threadIdx.x == 0) L.s_sg = atomicAdd(a.queue, 1u);
     __syncthreads();
@@ -371,19 +381,15 @@ __global__ __launch_bounds__(FR_THREADS) void frontier_resident_k(FrontierArgs a
     const uint32_t* drow = a.in_diff + (u64)sg * W;
     uint32_t nd = 0, nu = 0, tnd, tnu;
     for (uint32_t i = threadIdx.x; i < W; i += FR_THREADS) {
-      const uint32_t f = drow[i];
+      const uint32_t f = drow[i], v = grow[i];
       f_row[i] = f;
-      nd += __popc(f);
-    }
-    block_sum2(nd, 0u, &tnd, &tnu, L.s_w, L.s_w2);
-    if (tnd == 0) continue;  // no delta: the row stays as it is (block_sum2 ended with a barrier)
-    for (uint32_t i = threadIdx.x; i < W; i += FR_THREADS) {
-      const uint32_t v = grow[i];
       old_row[i] = v;
       new_row[i] = v;
+      nd += __popc(f);
       if (a.pull_ratio) nu += __popc(~v & a.hasin[i]);
     }
-    block_sum2(nu, 0u, &tnu, &nd, L.s_w, L.s_w2);
+    block_sum2(nd, nu, &tnd, &tnu, L.s_w, L.s_w2);
+    if (tnd == 0) continue;  // no delta: the row stays as it is (block_sum2 ended with a barrier)
     uint32_t round = 0;
     while (tnd > 0) {
       if (round >= a.max_rounds) {
@@ -409,11 +415,14 @@ __global__ __launch_bounds__(FR_THREADS) void frontier_resident_k(FrontierArgs a
         if (a.pull_ratio) nu += __popc(~nv & a.hasin[i]);
       }
       block_sum2(nd, nu, &tnd, &tnu, L.s_w, L.s_w2);
-      if (threadIdx.x == 0 && tnd) atomicAdd(&a.round_new[round < a.round_slots ? round : a.round_slots - 1], (u64)tnd);
+      if (threadIdx.x == 0 && tnd) {
+        if (round < FR_ROUNDS) s_round[round] += tnd;
+        else atomicAdd(&a.round_new[round < a.round_slots ? round : a.round_slots - 1], (u64)tnd);
+      }
       news += tnd;
       ++round;
     }
-    if (threadIdx.x == 0 && round) atomicMax(a.max_round, round);
+    max_round = max(max_round, round);
     if (round)
       for (uint32_t i = threadIdx.x; i < W; i += FR_THREADS) grow[i] = old_row[i];
     __syncthreads();  // the row is written before LDS takes the next key
@@ -422,11 +431,12 @@ __global__ __launch_bounds__(FR_THREADS) void frontier_resident_k(FrontierArgs a
   __shared__ u64 s_c[FR_WAVES];
   if (lane == 0) s_c[w] = cands;
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (w == 0) {
     u64 t = 0;
     for (int i = 0; i < FR_WAVES; ++i) t += s_c[i];
-    if (t) atomicAdd(&a.counters[CNT_CANDIDATES], t);
-    if (news) atomicAdd(&a.counters[CNT_APPENDED], news);
+    wave_counters_add(a.counters, news, 0, t);
+    if ((uint32_t)lane < min(FR_ROUNDS, a.round_slots) && s_round[lane]) atomicAdd(&a.round_new[lane], s_round[lane]);
+    if (lane == 0 && max_round) atomicMax(a.max_round, max_round);
   }
 }
 
@@ -513,11 +523,11 @@ __global__ __launch_bounds__(FR_THREADS) void gather_round_k(GatherArgs g) {
     }
     __syncthreads();  // the LDS rows and shared words are reused by the next row
   }
-  const u64 c = wave_incl_scan_t<u64>(cands), fr = wave_incl_scan_t<u64>(fresh);
-  if (lane == 63) {
-    if (c) atomicAdd(&g.counters[CNT_CANDIDATES], c);
-    if (fr) atomicAdd(&g.counters[CNT_APPENDED], fr);
+  for (int k = 32; k > 0; k >>= 1) {
+    cands += __shfl_xor(cands, k, 64);
+    fresh += __shfl_xor(fresh, k, 64);
   }
+  wave_counters_add(g.counters, fresh, 0, cands);
 }
 
 // Gathered round by delta row (GatherArgs::by_a).  Every X that e1 pairs
@@ -679,11 +689,11 @@ __global__ __launch_bounds__(64) void gather_by_a_k(GatherArgs g) {
     for (uint32_t wi = umin + (uint32_t)lane; wi < hi; wi += 64) U[wi] = 0u;
     wave_lds_sync();
   }
-  const u64 c = wave_incl_scan_t<u64>(cands), fr = wave_incl_scan_t<u64>(fresh);
-  if (lane == 63) {
-    if (c) atomicAdd(&g.counters[CNT_CANDIDATES], c);
-    if (fr) atomicAdd(&g.counters[CNT_APPENDED], fr);
+  for (int k = 32; k > 0; k >>= 1) {
+    cands += __shfl_xor(cands, k, 64);
+    fresh += __shfl_xor(fresh, k, 64);
   }
+  wave_counters_add(g.counters, fresh, 0, cands);
 }
 
 hipError_t gather_round(const GatherArgs& a, hipStream_t s) {

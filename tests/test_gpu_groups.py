@@ -1,0 +1,89 @@
+"""Grouped aggregates of non-recursive rules: groups that span lanes, wavefronts
+and single rows, in driver order and shuffled by a join, one and two key
+columns, dense and hashed heads, against numpy in the engine's arithmetic."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+RULES = """
+low(X,min(V)) :- e(X,Y,V).
+high(X,max(V)) :- e(X,Y,V).
+n(X,count(Y)) :- e(X,Y,_).
+total(X,sum(K)) :- f(X,Y,K).
+bylow(Y,min(V)) :- e(_,Y,V).
+pairhigh(X,Y,max(V)) :- e(X,Y,V).
+pairtotal(Y,X,sum(K)) :- f(X,Y,K).
+two(X,min(D)) :- e(X,Y,V), e(Y,_,U), D is V + U.
+"""
+F, I = ("i32", "f32"), ("i32", "i32")
+IDB = {"low": F, "high": F, "n": I, "total": I, "bylow": F, "pairhigh": ("i32", "i32", "f32"),
+       "pairtotal": ("i32", "i32", "i32"), "two": F}
+
+
+def _fold(keys, v, how):
+    order = np.lexsort(keys[::-1])
+    keys, v = [k[order] for k in keys], v[order]
+    start = np.ones(len(v), bool)
+    start[1:] = np.any([k[1:] != k[:-1] for k in keys], axis=0)
+    at = np.flatnonzero(start)
+    return [k[at] for k in keys] + [how.reduceat(v, at)]
+
+
+@pytest.mark.parametrize("index_mode", [0, 1])
+@pytest.mark.parametrize("shape", ["single_rows", "pairs", "tens", "waves", "hub", "negative"])
+def test_grouped_folds(shape, index_mode):
+    from paper_2609_27203_amd import xlh
+    print(f"case: groups {shape} index_mode={index_mode}", flush=True)
+    rng = np.random.default_rng(len(shape))
+    n = 6000
+    groups = {"single_rows": n, "pairs": n // 2, "tens": n // 10, "waves": 40, "hub": 3, "negative": 500}[shape]
+    x = rng.permutation(n) if shape == "single_rows" else rng.integers(0, groups, n)
+    y = rng.integers(0, groups, n)
+    if shape == "negative":
+        x, y = x - 250, y - 100
+    xy = np.unique(np.stack([x, y], 1), axis=0).astype(np.int32)
+    x, y = xy[:, 0].copy(), xy[:, 1].copy()
+    v = (rng.standard_normal(len(x)) * 10).astype(np.float32)
+    k = rng.integers(-1000, 1000, len(x)).astype(np.int32)
+    ctx = xlh.Context(device=0, workspace_bytes=1 << 30)
+    ctx.set_option("index_mode", index_mode)
+    ctx.relation("e", ("i32", "i32", "f32")).load([x, y, v])
+    ctx.relation("f", ("i32", "i32", "i32")).load([x, y, k])
+    for name, types in IDB.items():
+        ctx.relation(name, types)
+    ctx.compile(RULES).run()
+    lows = dict(zip(*[c.tolist() for c in _fold([x], v, np.minimum)]))
+    near = np.array([lows.get(int(b), np.inf) for b in y], np.float32)
+    ok = np.isfinite(near)
+    want = {"low": _fold([x], v, np.minimum), "high": _fold([x], v, np.maximum),
+            "n": _fold([x], np.ones(len(x), np.int32), np.add), "total": _fold([x], k, np.add),
+            "bylow": _fold([y], v, np.minimum), "pairhigh": _fold([x, y], v, np.maximum),
+            "pairtotal": _fold([y, x], k, np.add), "two": _fold([x[ok]], (v + near)[ok], np.minimum)}
+    for name, cols in want.items():
+        got = ctx.relations[name].read()
+        assert len(got[0]) == len(cols[0]), name
+        for g, w in zip(got, cols):
+            assert np.array_equal(g, w.astype(g.dtype)), name
+    ctx.close()
+
+
+@pytest.mark.parametrize("index_mode", [0, 1])
+def test_min_of_extreme_values(index_mode):
+    """Infinities and the largest finite values, alone and next to others in their group."""
+    from paper_2609_27203_amd import xlh
+    print(f"case: extreme values index_mode={index_mode}", flush=True)
+    big = np.finfo(np.float32).max
+    x = np.repeat(np.arange(6, dtype=np.int32), 3)
+    y = np.tile(np.arange(3, dtype=np.int32), 6)
+    v = np.float32([np.inf] * 3 + [-np.inf] * 3 + [big, np.inf, -big] + [-np.inf, np.inf, 0] + [0.0, 1e-45, -1e-45]
+                   + [np.inf, big, big])
+    ctx = xlh.Context(device=0, workspace_bytes=256 << 20)
+    ctx.set_option("index_mode", index_mode)
+    ctx.relation("e", ("i32", "i32", "f32")).load([x, y, v])
+    ctx.relation("low", F)
+    ctx.relation("high", F)
+    ctx.compile("low(X,min(V)) :- e(X,Y,V).\nhigh(X,max(V)) :- e(X,Y,V).").run()
+    assert np.array_equal(ctx.relations["low"].read()[1], v.reshape(6, 3).min(1))
+    assert np.array_equal(ctx.relations["high"].read()[1], v.reshape(6, 3).max(1))
+    ctx.close()
