@@ -826,6 +826,8 @@ struct HeadRun {
   int nkey = 1;
   bool once = false;  // head of a non-recursive stratum: no delta is kept
   bool lean = false;  // the same for dense values (unless the receipt counts listed slots)
+  bool sorted_set = false;  // set head of a scan: candidate keys, sorted and deduplicated at the end
+  bool in_order = false;    // the candidates ascend as they are
   KeyPack kp{};
   int bits0 = 1;      // width of the first packed key component
   double domain = 0;  // number of possible keys
@@ -1426,7 +1428,21 @@ struct Runner {
                                                 : (double)((range0 + 31) / 32) * 32.0;
         const double budget = c->index_mode == 2 ? (double)c->arena.capacity() / 2
                                                  : std::min(4294967296.0, (double)c->arena.capacity() / 4);
-        if (total_bits / 8 <= budget) {
+        // A set head whose rules only scan: at most as many candidates as
+        // driver rows, so a sort of their keys replaces a bitmap that is far
+        // larger than them (its clear, count and listing pass over every
+        // word: 300 + 780 + 240 us for 1.25 GB holding 0.9 M rows, 80
+        // as candidate keys), or a hash table whose rows every read would sort.
+        bool scans = hr->once && h->nrows == 0 && c->index_mode == 0;
+        double rows = 0;
+        for (const RulePlan& p : s.full) {
+          scans = scans && p.head == h && p.steps.empty();
+          rows += (double)p.driver->nrows;
+        }
+        if (scans && rows < 2147483648.0 &&
+            (total_bits / 8 > budget || total_bits / 8 > 33554432.0 + 160.0 * rows)) {
+          hr->sorted_set = true;
+        } else if (total_bits / 8 <= budget) {
           hr->dense = true;
           hr->range0 = range0;
           hr->row_bits = row_bits;
@@ -1619,6 +1635,7 @@ struct Runner {
     }
     if (h->dense) return init_dense(h);
     if (h->dcount) return init_dcount(h);
+    if (h->sorted_set || (h->is_sortagg && h->once)) return XL_OK;  // rows come from the sorted candidates
     h->cap = initial_cap(h->preloaded);
     XL_TRY(alloc_table(h, h->cap, &h->table));
     if (h->is_set) {
@@ -3330,7 +3347,12 @@ struct Runner {
         cands += (int64_t)cnt[CNT_CANDIDATES];
         return XL_OK;
       }
-      if (h->is_sortagg) {
+      if (h->is_sortagg || h->sorted_set) {
+        // candidates follow the driver's rows, so keys that are the leading
+        // columns of a driver in canonical order ascend already
+        bool lead = p.driver->sorted && !p.driver_delta && !head_of(p.driver);
+        for (int j = 0; j < p.nkey; ++j)
+          lead = lead && p.driver_act[j].kind == CA_BIND && p.driver_act[j].slot == p.key_slot[j];
         a.emit.mode = EM_MAT;
         a.emit.mat_packed = 1;
         int64_t total = 0;
@@ -3338,15 +3360,17 @@ struct Runner {
         XL_TRY(counted_pass(a, &total, &offs));
         cands += total;
         if (total == 0) return XL_OK;
+        h->in_order = h->cn == 0 && lead;
         const size_t kb = key_bytes(h);
         if (h->cn + total > h->ccap) {
           const int64_t ncap = std::max<int64_t>(h->cn + total, h->ccap * 2);
           Buf nk, nv;
           XL_TRY(dalloc(c, (size_t)ncap * kb, &nk, "aggregate candidates"));
-          XL_TRY(dalloc(c, (size_t)ncap * 4, &nv, "aggregate candidates"));
+          if (!h->sorted_set) XL_TRY(dalloc(c, (size_t)ncap * 4, &nv, "aggregate candidates"));
           if (h->cn) {
             HIP_TRY(c, hipMemcpyAsync(nk.p, h->ckey.p, (size_t)h->cn * kb, hipMemcpyDeviceToDevice, c->stream));
-            HIP_TRY(c, hipMemcpyAsync(nv.p, h->cval.p, (size_t)h->cn * 4, hipMemcpyDeviceToDevice, c->stream));
+            if (!h->sorted_set)
+              HIP_TRY(c, hipMemcpyAsync(nv.p, h->cval.p, (size_t)h->cn * 4, hipMemcpyDeviceToDevice, c->stream));
           }
           std::swap(h->ckey.p, nk.p);
           std::swap(h->cval.p, nv.p);
@@ -3486,6 +3510,7 @@ struct Runner {
     h->round_begin = h->nrows;
     h->didx_n = 0;
     h->cn = 0;
+    h->in_order = false;
   }
 
   xl_status finish_round(HeadRun* h, int64_t* delta) {
@@ -3497,6 +3522,10 @@ struct Runner {
     if (h->gathered && h->gather_ready) {  // a gathered round wrote the next delta rows
       h->gcur ^= 1;
       *delta = h->fnew;
+      return XL_OK;
+    }
+    if (h->sorted_set) {  // its rows are made at materialization
+      *delta = 0;
       return XL_OK;
     }
     if (h->once && (h->dense || h->is_minmax)) {  // no round follows
@@ -3630,16 +3659,18 @@ struct Runner {
     const int kbits = h->nkey == 2 ? h->bits0 + h->kp.shift : h->bits0;
     const int kb = (int)key_bytes(h);
     Buf k2, v2, tmp, flag, pos, tot;
-    XL_TRY(dalloc(c, (size_t)n * kb, &k2, "sort keys"));
-    XL_TRY(dalloc(c, (size_t)n * 4, &v2, "sort values"));
-    XL_TRY(dalloc(c, k::radix_temp_bytes(n), &tmp, "sort scratch"));
     int alt = 0;
-    if (kb == 4)
-      HIP_TRY(c, k::radix_sort_u32(h->ckey.as<uint32_t>(), h->cval.as<uint32_t>(), k2.as<uint32_t>(),
-                                   v2.as<uint32_t>(), n, kbits, tmp.p, c->stream, &alt));
-    else
-      HIP_TRY(c, k::radix_sort_u64(h->ckey.as<u64>(), h->cval.as<uint32_t>(), k2.as<u64>(), v2.as<uint32_t>(),
-                                   n, kbits, tmp.p, c->stream, &alt));
+    if (!h->in_order) {
+      XL_TRY(dalloc(c, (size_t)n * kb, &k2, "sort keys"));
+      XL_TRY(dalloc(c, (size_t)n * 4, &v2, "sort values"));
+      XL_TRY(dalloc(c, k::radix_temp_bytes(n), &tmp, "sort scratch"));
+      if (kb == 4)
+        HIP_TRY(c, k::radix_sort_u32(h->ckey.as<uint32_t>(), h->cval.as<uint32_t>(), k2.as<uint32_t>(),
+                                     v2.as<uint32_t>(), n, kbits, tmp.p, c->stream, &alt));
+      else
+        HIP_TRY(c, k::radix_sort_u64(h->ckey.as<u64>(), h->cval.as<uint32_t>(), k2.as<u64>(), v2.as<uint32_t>(),
+                                     n, kbits, tmp.p, c->stream, &alt));
+    }
     void* sk = alt ? k2.p : h->ckey.p;
     uint32_t* sv = alt ? v2.as<uint32_t>() : h->cval.as<uint32_t>();
     XL_TRY(dalloc(c, (size_t)n * 4, &flag, "segment flags"));
@@ -3671,6 +3702,15 @@ struct Runner {
       XL_TRY(ctl_read(c, c->dcounters, sizeof(cnt), cnt));
       if (cnt[CNT_FATAL]) return c->fail(XL_DEVICE_ERROR, "key outside the dense domain (internal)");
       h->keys += (int64_t)cnt[CNT_INSERTED];
+      if (h->rel->max_rows > 0 && h->keys > h->rel->max_rows)
+        return c->fail(XL_CAPACITY_EXCEEDED, "relation " + h->rel->name + " exceeds its max_rows");
+      h->dn = nseg;
+      h->cn = 0;
+      *delta = nseg;
+      return XL_OK;
+    }
+    if (h->once) {  // nothing to merge with: the folded rows are the relation
+      h->keys = nseg;
       if (h->rel->max_rows > 0 && h->keys > h->rel->max_rows)
         return c->fail(XL_CAPACITY_EXCEEDED, "relation " + h->rel->name + " exceeds its max_rows");
       h->dn = nseg;
@@ -3856,6 +3896,16 @@ struct Runner {
       for (int j = 0; j <= h->nkey; ++j) r->col[j] = (uint32_t*)out[j].keep();
       r->nrows = n;
       r->sorted = true;  // rows rank by rank: ascending keys
+    } else if (h->sorted_set) {
+      return materialize_sorted_set(h);
+    } else if (h->is_sortagg && h->once) {  // folded in key order
+      Buf none[3];
+      for (int j = 0; j <= h->nkey; ++j)
+        if (!h->drow[j].p) XL_TRY(dalloc(c, 4, &none[j], "relation column"));
+      relation_free_storage(r);
+      for (int j = 0; j <= h->nkey; ++j) r->col[j] = (uint32_t*)(h->drow[j].p ? h->drow[j] : none[j]).keep();
+      r->nrows = h->keys;
+      r->sorted = true;
     } else if (h->is_set) {
       relation_free_storage(r);
       for (int j = 0; j < h->nkey; ++j) r->col[j] = (uint32_t*)h->rows[j].keep();
@@ -3880,6 +3930,64 @@ struct Runner {
       r->nrows = n;
       r->key_cols = h->nkey;
     }
+    return XL_OK;
+  }
+
+  // Rows of a sorted set head: its candidate keys sorted (unless they ascend
+  // already), the distinct ones unpacked.
+  xl_status materialize_sorted_set(HeadRun* h) {
+    Relation* r = h->rel;
+    const int64_t n = h->cn;
+    Buf out[2];
+    uint32_t m = 0;
+    if (n == 0) {
+      for (int j = 0; j < h->nkey; ++j) XL_TRY(dalloc(c, 4, &out[j], "relation column"));
+    } else {
+      const bool wide = key_bytes(h) == 8;
+      const int kbits = h->nkey == 2 ? h->bits0 + h->kp.shift : h->bits0;
+      Buf k2, tmp, cnt, off, tot;
+      int alt = 0;
+      if (!h->in_order) {
+        XL_TRY(dalloc(c, (size_t)n * (wide ? 8 : 4), &k2, "sort keys"));
+        XL_TRY(dalloc(c, k::radix_temp_bytes(n), &tmp, "sort scratch"));
+        if (wide)
+          HIP_TRY(c, k::radix_sort_u64(h->ckey.as<u64>(), nullptr, k2.as<u64>(), nullptr, n, kbits, tmp.p, c->stream,
+                                       &alt));
+        else
+          HIP_TRY(c, k::radix_sort_u32(h->ckey.as<uint32_t>(), nullptr, k2.as<uint32_t>(), nullptr, n, kbits, tmp.p,
+                                       c->stream, &alt));
+      }
+      const void* sk = alt ? k2.p : h->ckey.p;
+      const int64_t nt = k::row_tiles(n);
+      XL_TRY(dalloc(c, (size_t)nt * 4, &cnt, "row counts"));
+      XL_TRY(dalloc(c, (size_t)nt * 4, &off, "row offsets"));
+      XL_TRY(dalloc(c, k::scan_temp_bytes(nt), &tmp, "scan scratch"));
+      XL_TRY(dalloc(c, 8, &tot, "count"));
+      HIP_TRY(c, k::count_rows(sk, wide, nullptr, n, cnt.as<uint32_t>(), c->stream));
+      HIP_TRY(c, k::scan_exclusive_u32(cnt.as<uint32_t>(), off.as<uint32_t>(), nt, tot.as<uint32_t>(), tmp.p,
+                                       c->stream));
+      XL_TRY(ctl_read(c, tot.p, 4, &m));
+      if (r->max_rows > 0 && (int64_t)m > r->max_rows)
+        return c->fail(XL_CAPACITY_EXCEEDED, "relation " + r->name + " exceeds its max_rows " +
+                                                 std::to_string(r->max_rows));
+      k::RowPack rp{};
+      rp.by = h->nkey;
+      for (int j = 0; j < h->nkey; ++j) {
+        XL_TRY(dalloc(c, (size_t)m * 4, &out[j], "relation column"));
+        const int bits = j == 0 ? h->bits0 : h->kp.shift;
+        rp.type[j] = T_I32;
+        rp.lo[j] = (uint32_t)h->kp.lo[j] ^ 0x80000000u;
+        rp.mask[j] = bits >= 32 ? 0xffffffffu : (1u << bits) - 1u;
+        rp.shift[j] = j == 0 && h->nkey == 2 ? h->kp.shift : 0;
+        rp.ltype[j] = XL_I32;  // stored images stay as they are
+        rp.dst[j] = out[j].p;
+      }
+      HIP_TRY(c, k::unpack_rows(rp, sk, wide, nullptr, n, off.as<uint32_t>(), c->stream));
+    }
+    relation_free_storage(r);
+    for (int j = 0; j < h->nkey; ++j) r->col[j] = (uint32_t*)out[j].keep();
+    r->nrows = h->keys = m;
+    r->sorted = true;
     return XL_OK;
   }
 

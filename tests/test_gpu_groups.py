@@ -87,3 +87,77 @@ def test_min_of_extreme_values(index_mode):
     assert np.array_equal(ctx.relations["low"].read()[1], v.reshape(6, 3).min(1))
     assert np.array_equal(ctx.relations["high"].read()[1], v.reshape(6, 3).max(1))
     ctx.close()
+
+
+SCAN_RULES = """
+same(X,Y) :- e(X,Y).
+turned(Y,X) :- e(X,Y).
+either(X,Y) :- e(X,Y).
+either(X,Y) :- e(Y,X), X != 7.
+first(X) :- e(X,_).
+second(Y) :- e(_,Y), not first(Y).
+none(X,Y) :- e(X,Y), X < -5.
+joined(X,Z) :- same(X,Y), turned(Y,Z), X != Z.
+"""
+
+
+@pytest.mark.parametrize("index_mode", [0, 1])
+@pytest.mark.parametrize("n", [1, 3, 2047, 2049, 70_000])
+@pytest.mark.parametrize("span", [2**17, 2**31 - 8])
+def test_scanned_sets_over_wide_domains(n, span, index_mode):
+    """Set heads of scans whose bitmap would be far larger than their rows (sorted
+    candidate keys of 32 and 64 bits), and rules that join them afterwards."""
+    from paper_2609_27203_amd import xlh
+    print(f"case: scanned sets n={n} span={span} index_mode={index_mode}", flush=True)
+    rng = np.random.default_rng(n)
+    x = np.r_[0, span, rng.integers(0, span, n)].astype(np.int32)
+    y = np.r_[span, 5, rng.integers(0, span, n)].astype(np.int32)
+    ctx = xlh.Context(device=0, workspace_bytes=1 << 30)
+    ctx.set_option("index_mode", index_mode)
+    ctx.set_option("hash_min_log2", 18)
+    ctx.relation("e", I).load([x, y])
+    two = ("same", "turned", "either", "none", "joined")
+    for name in two:
+        ctx.relation(name, I)
+    for name in ("first", "second"):
+        ctx.relation(name, ("i32",))
+    stats = ctx.compile(SCAN_RULES).run()
+    e = set(zip(x.tolist(), y.tolist()))
+    back = {}
+    for a, b in e:
+        back.setdefault(b, []).append(a)
+    firsts = {a for a, _ in e}
+    want = {"same": e, "turned": {(b, a) for a, b in e}, "none": set(),
+            "either": e | {(b, a) for a, b in e if b != 7},
+            "joined": {(a, c) for a, b in e for c in back[b] if a != c},
+            "first": {(a,) for a in firsts}, "second": {(b,) for _, b in e if b not in firsts}}
+    for name, rows in want.items():
+        got = ctx.relations[name].read()
+        assert list(zip(*[c.tolist() for c in got])) == sorted(rows), name
+    assert stats["derived_tuples"] == sum(len(r) for r in want.values())
+    ctx.close()
+
+
+def test_scanned_set_capacity_and_resume():
+    """max_rows bounds the distinct rows; a relation with rows keeps them."""
+    from paper_2609_27203_amd import xlh
+    print("case: scanned set capacity and resume", flush=True)
+    x = np.arange(1000, dtype=np.int32) * 1_000_003 % 2**30
+    for limit, ok in ((1000, True), (999, False)):
+        ctx = xlh.Context(device=0, workspace_bytes=256 << 20)
+        ctx.relation("e", I).load([np.r_[x, x], np.r_[x, x]])
+        ctx.relation("f", I).load([np.r_[x, x], np.r_[x[::-1], x]])
+        out = ctx.relation("out", I, max_rows=limit)
+        prog = ctx.compile("out(X,Y) :- e(X,Y).\nout(Y,X) :- e(X,Y).")
+        if not ok:
+            with pytest.raises(xlh.XlError) as ei:
+                prog.run()
+            assert ei.value.status_name == "XL_CAPACITY_EXCEEDED"
+            continue
+        prog.run()
+        assert out.size() == 1000
+        out.load([np.int32([3]), np.int32([4])])
+        ctx.relation("more", I)
+        with pytest.raises(xlh.XlError):  # 1,001 rows now
+            prog.run()
+        ctx.close()
