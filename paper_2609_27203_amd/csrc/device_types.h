@@ -397,6 +397,9 @@ struct WcojArgs {
   int32_t probe_shorter;    // 1: probe the shorter list; 0: always b's (the binary-join order)
   uint32_t* work;           // [na] items of row i (work pass)
   const uint32_t* crow;     // [nz] driver rows with items, ascending
+  uint32_t* seg;            // [3][nz] first row of each one's shorter list and of its longer list, and the
+                            // longer list's length (bit 31: the shorter list is c's)
+  unsigned long long* mask; // [chunks][WC_CHUNK / 64] hits of the count pass (null: the write pass probes again)
   const unsigned long long* cofs;  // [nz + 1] first item of each such row
   int64_t nz;
   unsigned long long items;

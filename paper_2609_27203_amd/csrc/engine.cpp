@@ -508,6 +508,33 @@ xl_status relation_clear(Relation* r) {
 // ================================================================== load / read
 namespace {
 
+// A load of few rows in one launch; *done stays false when the rows need more
+// than 64 bits.
+xl_status load_small(Context* c, const Relation* r, const uint32_t* const* rc, int64_t n, uint32_t* lo, uint32_t* hi,
+                     Buf* fin, int64_t* m, bool* done) {
+  k::RowPack p{};
+  Buf out;
+  p.by = r->arity;
+  for (int j = 0; j < r->arity; ++j) {
+    XL_TRY(dalloc(c, (size_t)n * 4, &fin[j], "relation column"));
+    p.col[j] = rc[j];
+    p.type[j] = r->types[j];
+    p.dst[j] = fin[j].p;
+  }
+  XL_TRY(dalloc(c, 4 * (1 + 2 * MAXC), &out, "load result"));
+  HIP_TRY(c, k::load_small(p, n, out.as<uint32_t>(), c->stream));
+  uint32_t t[1 + 2 * MAXC];
+  XL_TRY(ctl_read(c, out.p, sizeof(t), t));
+  *done = t[0] > 0;
+  *m = t[0];
+  for (int j = 0; j < r->arity; ++j) {
+    if (!*done) fin[j].reset();
+    lo[j] = t[1 + 2 * j];
+    hi[j] = t[2 + 2 * j];
+  }
+  return XL_OK;
+}
+
 // The distinct rows of the loaded columns in canonical order, by one sort of
 // packed keys.  *done stays false when the columns do not fit a key and a
 // payload, when the workspace does not hold the sort, or when more rows than
@@ -634,15 +661,12 @@ xl_status relation_load(Relation* r, const void* const* cols, int64_t n, int on_
   Buf fin[MAXC];
   int64_t m = 0;
   uint32_t lo[MAXC], hi[MAXC];
-  XL_TRY(image_bounds(c, rc, r->types, r->arity, n, lo, hi));
-  bool done = n == 1;
-  if (done) {
-    m = 1;
-    for (int j = 0; j < r->arity; ++j) {
-      XL_TRY(dalloc(c, 4, &fin[j], "relation column"));
-      HIP_TRY(c, hipMemcpyAsync(fin[j].p, rc[j], 4, hipMemcpyDeviceToDevice, c->stream));
-    }
-  } else {
+  bool done = false;
+  if (n <= k::load_small_max()) {
+    XL_TRY(load_small(c, r, rc, n, lo, hi, fin, &m, &done));
+  }
+  if (!done) {
+    XL_TRY(image_bounds(c, rc, r->types, r->arity, n, lo, hi));
     XL_TRY(load_packed(c, r, rc, raw, n, lo, hi, fin, &m, &done));
   }
   if (!done) {
@@ -1317,6 +1341,9 @@ struct Runner {
   }
 
   xl_status setup_heads(Stratum& s) {
+    joined_rows = 0;
+    for (const RulePlan& p : s.variants)
+      for (const StepPlan& sp : p.steps) joined_rows = std::max(joined_rows, sp.rel->nrows);
     std::map<Relation*, std::vector<Interval>> dom;
     for (Relation* h : s.heads) {
       const Agg a = prog->head_agg(h);
@@ -1481,10 +1508,21 @@ struct Runner {
     return XL_OK;
   }
 
-  int64_t initial_cap(int64_t expect) {
+  // First capacity of a head's hash table.  A recursive set head starts at
+  // eight slots per row of the largest relation its rules join (within 1/32 of
+  // the free workspace): batched rounds use as many wavefronts as a quarter of the
+  // slots allows, and a growth inserts every row again.  16 sources over
+  // 200,000 nodes and 800,000 edges, evaluate and read: 1.67 ms from 4 M slots,
+  // 1.30 from 8 M.  A smaller
+  // hash_min_log2 than the default asks for small tables.
+  int64_t initial_cap(const HeadRun* h, int64_t expect) {
     int64_t cap = (int64_t)1 << c->hash_min_log2;
+    if (h->is_set && !h->once && c->hash_min_log2 >= 22)
+      cap = std::max(cap, std::min((int64_t)next_pow2((uint64_t)joined_rows * 8),
+                                   (int64_t)next_pow2(c->arena.largest_free() / 32 / 16 + 1) / 2));
     return (int64_t)std::max<uint64_t>(cap, next_pow2((uint64_t)std::max<int64_t>(expect, 1) * 4));
   }
+  int64_t joined_rows = 0;  // rows of the largest relation outside the stratum that a variant joins
 
   xl_status init_dense(HeadRun* h) {
     Relation* r = h->rel;
@@ -1636,7 +1674,7 @@ struct Runner {
     if (h->dense) return init_dense(h);
     if (h->dcount) return init_dcount(h);
     if (h->sorted_set || (h->is_sortagg && h->once)) return XL_OK;  // rows come from the sorted candidates
-    h->cap = initial_cap(h->preloaded);
+    h->cap = initial_cap(h, h->preloaded);
     XL_TRY(alloc_table(h, h->cap, &h->table));
     if (h->is_set) {
       h->rows_cap = h->cap;
@@ -4057,11 +4095,17 @@ struct Runner {
     uint32_t nz = 0;
     XL_TRY(ctl_read(c, tot.p, 4, &nz));
     if (nz == 0) return finish(0);
+    flags.reset();
+    Buf seg;
     XL_TRY(dalloc(c, (size_t)nz * 4, &crow, "triangle rows"));
     XL_TRY(dalloc(c, (size_t)(nz + 1) * 8, &cw, "triangle row work"));
+    XL_TRY(dalloc(c, (size_t)nz * 12, &seg, "triangle row lists"));
+    a.seg = seg.as<uint32_t>();
+    HIP_TRY(c, k::wcoj_compact(a, flag_pos.as<uint32_t>(), nz, crow.as<uint32_t>(), cw.as<unsigned long long>(),
+                               c->stream));
+    work.reset();
+    flag_pos.reset();
     XL_TRY(dalloc(c, (size_t)(nz + 1) * 8, &cofs, "triangle row offsets"));
-    HIP_TRY(c, k::wcoj_compact(work.as<uint32_t>(), flag_pos.as<uint32_t>(), a.na, crow.as<uint32_t>(),
-                               cw.as<unsigned long long>(), c->stream));
     XL_TRY(dalloc(c, k::scan_temp_bytes(nz), &tmp, "scan scratch"));
     HIP_TRY(c, k::scan_exclusive_u64(cw.as<u64>(), cofs.as<u64>(), nz, cofs.as<u64>() + nz, tmp.p, c->stream));
     u64 items = 0;
@@ -4077,6 +4121,11 @@ struct Runner {
     XL_TRY(dalloc(c, (size_t)nchunks * 4, &coff, "chunk offsets"));
     XL_TRY(dalloc(c, k::scan_temp_bytes((int64_t)nchunks), &tmp2, "scan scratch"));
     a.chunk_cnt = ccnt.as<uint32_t>();
+    // one bit per probe, kept by the count pass for the write pass; without
+    // room for it the write pass probes again
+    Buf mask;
+    if (dalloc(c, (size_t)nchunks * (k::WC_CHUNK / 8), &mask, "triangle hits") != XL_OK) mask.reset();
+    a.mask = mask.as<u64>();
     float ms_total = 0;
     auto timed = [&](bool mat) -> xl_status {
       if (c->profile) HIP_TRY(c, hipEventRecord(ev[0], c->stream));
@@ -4099,7 +4148,15 @@ struct Runner {
       return c->fail(XL_CAPACITY_EXCEEDED, "relation " + h->name + " exceeds its max_rows " +
                                                std::to_string(h->max_rows));
     Buf out[3];
-    for (int j = 0; j < 3; ++j) XL_TRY(dalloc(c, (size_t)std::max<uint32_t>(n, 1) * 4, &out[j], "relation column"));
+    for (int j = 0; j < 3; ++j) {
+      xl_status got = dalloc(c, (size_t)std::max<uint32_t>(n, 1) * 4, &out[j], "relation column");
+      if (got != XL_OK && mask.p) {
+        mask.reset();
+        a.mask = nullptr;
+        got = dalloc(c, (size_t)std::max<uint32_t>(n, 1) * 4, &out[j], "relation column");
+      }
+      XL_TRY(got);
+    }
     a.chunk_off = coff.as<uint32_t>();
     a.out0 = out[0].as<uint32_t>();
     a.out1 = out[1].as<uint32_t>();

@@ -76,9 +76,10 @@ constexpr int WC_CHUNK = 256;  // items per wavefront chunk
 hipError_t wcoj_work(const WcojArgs& a, hipStream_t s);
 // flag[i] = v[i] != 0
 hipError_t nonzero_flags(const uint32_t* v, int64_t n, uint32_t* flag, hipStream_t s);
-// crow[pos[i]] = i and cw[pos[i]] = work[i] for rows with work
-hipError_t wcoj_compact(const uint32_t* work, const uint32_t* pos, int64_t n, uint32_t* crow,
-                        unsigned long long* cw, hipStream_t s);
+// The nz rows with work: crow[pos[i]] = i, cw[pos[i]] = work[i] and the row's
+// lists in a.seg.
+hipError_t wcoj_compact(const WcojArgs& a, const uint32_t* pos, int64_t nz, uint32_t* crow, unsigned long long* cw,
+                        hipStream_t s);
 hipError_t wcoj_probe(const WcojArgs& a, bool materialize, hipStream_t s);
 // out[i] = key[i] >> shift, over 32-bit (wide false) or 64-bit keys
 hipError_t high_bits(const void* key, bool wide, int shift, int64_t n, uint32_t* out, hipStream_t s);
@@ -322,6 +323,11 @@ int64_t row_tiles(int64_t n);
 hipError_t count_rows(const void* key, bool wide, const uint32_t* pay, int64_t n, uint32_t* cnt, hipStream_t s);
 hipError_t unpack_rows(const RowPack& r, const void* key, bool wide, const uint32_t* pay, int64_t n,
                        const uint32_t* off, hipStream_t s);
+
+// A load of at most load_small_max() rows in one launch (see the kernel):
+// columns col[0 .. by) with types, dst[j] of n values; out: 1 + 2 * MAXC words.
+int64_t load_small_max();
+hipError_t load_small(const RowPack& r, int64_t n, uint32_t* out, hipStream_t s);
 
 }  // namespace k
 }  // namespace xlh

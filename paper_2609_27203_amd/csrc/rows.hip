@@ -17,6 +17,7 @@
 #include "../../include/xlh.h"
 #include "device_util.h"
 #include "kernels.h"
+#include "small_sort.h"
 
 namespace xlh {
 namespace k {
@@ -221,6 +222,112 @@ hipError_t unpack_rows(const RowPack& r, const void* key, bool wide, const uint3
   const unsigned g = (unsigned)row_tiles(n);
   if (wide) unpack_rows_k<u64, false><<<g, RW_THREADS, 0, s>>>(r, (const u64*)key, pay, n, nullptr, off);
   else unpack_rows_k<uint32_t, false><<<g, RW_THREADS, 0, s>>>(r, (const uint32_t*)key, pay, n, nullptr, off);
+  return hipGetLastError();
+}
+
+// A whole load of at most SS_MAX rows in one launch of one workgroup: bounds,
+// packing, sort, deduplication and unpacking (r: columns, types, ltypes and
+// dst, by = the column count; dst hold n values).  out[0] = distinct rows, or
+// 0 when the packed rows need more than 64 bits (nothing is written then);
+// out[1 + 2j], out[2 + 2j] = least and greatest image of column j.  Bound by
+// its barriers; the separate kernels cost eight launches and a second host
+// read (300 edges loaded, closed and read back: 251 -> 229 us).
+__global__ __launch_bounds__(SS_THREADS) void load_small_k(RowPack r, int n, uint32_t* out) {
+  __shared__ SmallSort<u64, false> L;
+  __shared__ uint32_t s_lo[MAXC][SS_WAVES], s_hi[MAXC][SS_WAVES], s_c[SS_WAVES * SS_ITEMS];
+  const int lane = lane_id(), w = threadIdx.x >> 6;
+  uint32_t img[MAXC][SS_ITEMS];
+#pragma unroll
+  for (int c = 0; c < MAXC; ++c) {
+    if (c >= r.by) continue;
+    uint32_t lo = 0xffffffffu, hi = 0;
+#pragma unroll
+    for (int j = 0; j < SS_ITEMS; ++j) {
+      const int p = ss_place(j);
+      img[c][j] = p < n ? row_image(r.col[c][p], r.type[c]) : 0u;
+      if (p < n) {
+        lo = min(lo, img[c][j]);
+        hi = max(hi, img[c][j]);
+      }
+    }
+    for (int d = 32; d > 0; d >>= 1) {
+      lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
+      hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
+    }
+    if (lane == 0) {
+      s_lo[c][w] = lo;
+      s_hi[c][w] = hi;
+    }
+  }
+  __syncthreads();
+  uint32_t lo[MAXC] = {}, width[MAXC] = {}, total = 0;
+#pragma unroll
+  for (int c = 0; c < MAXC; ++c) {
+    if (c >= r.by) continue;
+    uint32_t hi = 0;
+    lo[c] = 0xffffffffu;
+    for (int k = 0; k < SS_WAVES; ++k) {
+      lo[c] = min(lo[c], s_lo[c][k]);
+      hi = max(hi, s_hi[c][k]);
+    }
+    width[c] = 32u - (uint32_t)__clz((int)(hi - lo[c]));
+    total += width[c];
+    if (threadIdx.x == 0) {
+      out[1 + 2 * c] = lo[c];
+      out[2 + 2 * c] = hi;
+    }
+  }
+  if (total > 64) {
+    if (threadIdx.x == 0) out[0] = 0;
+    return;
+  }
+  u64 key[SS_ITEMS];
+  uint32_t none[SS_ITEMS] = {};
+#pragma unroll
+  for (int j = 0; j < SS_ITEMS; ++j) {
+    key[j] = 0;
+#pragma unroll
+    for (int c = 0; c < MAXC; ++c)
+      if (c < r.by && width[c]) key[j] = (width[c] < 64 ? key[j] << width[c] : 0) | (img[c][j] - lo[c]);
+  }
+  small_sort<u64, false>(key, none, n, (int)total, L);
+#pragma unroll
+  for (int j = 0; j < SS_ITEMS; ++j) L.sk[ss_place(j)] = key[j];
+  __syncthreads();
+  u64 keep[SS_ITEMS];
+#pragma unroll
+  for (int j = 0; j < SS_ITEMS; ++j) {
+    const int p = ss_place(j);
+    keep[j] = __ballot(p < n && (p == 0 || L.sk[p - 1] != key[j]));
+    if (lane == 0) s_c[w * SS_ITEMS + j] = (uint32_t)__popcll(keep[j]);
+  }
+  __syncthreads();
+  if (w == 0) {  // exclusive prefix of the 64 counts, in row order
+    const uint32_t c = s_c[lane], incl = wave_incl_scan(c);
+    s_c[lane] = incl - c;
+    if (lane == 63) out[0] = incl;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < SS_ITEMS; ++j) {
+    if (!((keep[j] >> lane) & 1ull)) continue;
+    const uint32_t o = s_c[w * SS_ITEMS + j] + (uint32_t)__popcll(keep[j] & lanemask_lt());
+    u64 k = key[j];
+#pragma unroll
+    for (int c = MAXC - 1; c >= 0; --c) {
+      if (c >= r.by) continue;
+      const uint32_t image = (uint32_t)(k & (width[c] >= 32 ? 0xffffffffull : (1ull << width[c]) - 1ull)) + lo[c];
+      k >>= width[c];
+      ((uint32_t*)r.dst[c])[o] = row_value(image, r.type[c]);
+    }
+  }
+}
+static_assert(SS_WAVES * SS_ITEMS == 64, "one lane per count");
+
+int64_t load_small_max() { return SS_MAX; }
+hipError_t load_small(const RowPack& r, int64_t n, uint32_t* out, hipStream_t s) {
+  if (n <= 0 || n > SS_MAX || r.by <= 0 || r.by > MAXC) return hipErrorInvalidValue;
+  load_small_k<<<1, SS_THREADS, 0, s>>>(r, (int)n, out);
   return hipGetLastError();
 }
 
