@@ -38,12 +38,15 @@ struct MicroOp {
 // A negated literal not q(...) over a complete relation q: the sorted keys
 // of q's rows projected onto the literal's constrained columns (variables and
 // constants; none, one, or two int32 columns packed (v0 << 32) | v1 as
-// unsigned), searched per candidate.  With no constrained column the literal
-// only asks whether q has a row (n > 0).
+// unsigned), searched per candidate; or, for one column over a range not much
+// wider than its rows, a bitmap of its values (bit v - lo, v - lo < range).
+// With no constrained column the literal only asks whether q has a row (n > 0).
 constexpr int MAXNEG = 2;
 struct NegTable {
   const unsigned long long* keys;
   int64_t n;
+  const uint32_t* bits;
+  uint32_t lo, range;
 };
 
 // Rows that drive a stage: a relation, a delta, or materialized bindings
@@ -62,10 +65,14 @@ struct RowSource {
 //   compacted (keys != nullptr): keys[0 .. key_range) are the distinct key
 //     values minus key_lo (as unsigned, ascending) and off[i] .. off[i+1]
 //     delimit the rows of keys[i] (sparse or wide key ranges, found by
-//     binary search).
+//     binary search).  With bucket, the keys whose value >> bshift is b are
+//     keys[bucket[b] .. bucket[b + 1]), b < buckets, and only those are
+//     searched.
 struct IndexProbe {
   const uint32_t* off;
   const uint32_t* keys;
+  const uint32_t* bucket;
+  uint32_t buckets, bshift;
   const uint32_t* col[MAXC];
   int32_t ncols;
   int32_t key_lo;
@@ -121,6 +128,7 @@ enum Counter : int32_t {
 enum CheckBit : unsigned long long {
   CHECK_BITMAP_ROWS = 1,    // a dense head's bitmap holds a different row count than its receipt
   CHECK_COUNT_DOMAIN = 2,   // a count key outside the head's planned domain
+  CHECK_VALUE_ROWS = 4,     // a value head holds a different row count than its receipt
 };
 
 struct EmitSpec {

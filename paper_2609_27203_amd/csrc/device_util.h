@@ -21,6 +21,12 @@ __device__ __forceinline__ bool index_segment(const IndexProbe& ix, uint32_t v, 
     return kk < ix.key_range;
   }
   uint32_t lo = 0, len = ix.key_range;  // first distinct key >= kk
+  if (ix.bucket) {  // (a value below key_lo wraps to a bucket past the last, or to keys all below it)
+    const uint32_t b = kk >> ix.bshift;
+    if (b >= ix.buckets) return false;
+    lo = ix.bucket[b];
+    len = ix.bucket[b + 1] - lo;
+  }
   while (len > 0) {
     const uint32_t half = len >> 1;
     if (ix.keys[lo + half] < kk) {

@@ -223,3 +223,17 @@ def test_readout_of_hash_tables(span, value, labels):
                 at = shift if j else 0
                 assert np.array_equal(x.cpu().numpy()[at:at + w.nbytes], w.view(np.uint8))
     ctx.close()
+
+
+@pytest.mark.parametrize("name", list(WIDTHS))
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 255, 257, 1000, 3071])
+def test_small_loads(name, n):
+    """Loads of one workgroup: every column layout, duplicates, rows of one value."""
+    types, make = WIDTHS[name]
+    cols = make(np.random.default_rng(n), n)
+    cols = [np.ascontiguousarray(np.r_[c, c[: len(c) // 3]])[:4096] for c in cols]
+    want = _canonical_bits(cols)
+    for device, shift in ((False, 0), (True, 0), (True, 2)):
+        print(f"case: small load {name} n={n} device={device} shift={shift}", flush=True)
+        for g, w in zip(_load_and_read(types, cols, device, shift, 8 << 20), want):
+            assert np.array_equal(g.view(np.uint32), w.view(np.uint32))
