@@ -272,6 +272,7 @@ struct DenseTileArgs {
   // 1 / 2: the rule is "value is P1 + / - e.col[fcol]" with nothing else to
   // check, evaluated directly instead of through the micro-op list
   int8_t fast, fcol;
+  const uint2* pairs;     // fast: (Y - first Y of its tile, e.col[fcol]) of every row in index order
   int32_t nops;
   MicroOp ops[MAXOPS];
   uint32_t consts[MAXK];

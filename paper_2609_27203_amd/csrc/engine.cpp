@@ -3057,17 +3057,26 @@ struct Runner {
                                  n, std::max(1, key_bits), tmp.p, c->stream, &alt));
     uint32_t* sk = alt ? keys2.as<uint32_t>() : keys.as<uint32_t>();
     uint32_t* spm = alt ? perm2.as<uint32_t>() : perm.as<uint32_t>();
-    uint32_t* tc[MAXC] = {};
-    for (int j = 0; j < e->arity; ++j) {
+    int fcol = 0;
+    if (affine_value(p, &fcol)) {
       h->tcols.push_back(std::make_unique<Buf>());
-      XL_TRY(dalloc(c, (size_t)n * 4, h->tcols.back().get(), "tiled index column"));
-      tc[j] = h->tcols.back()->as<uint32_t>();
-      q.col[j] = tc[j];
+      XL_TRY(dalloc(c, (size_t)n * 8, h->tcols.back().get(), "tiled index pairs"));
+      HIP_TRY(c, k::tile_pairs(spm, e->col[zc], e->col[p.carried_ycol], e->col[fcol], n, e->lo[zc], h->kp.lo[1],
+                               h->tile, h->ntiles, (uint32_t)zr, h->tcols.back()->p, presorted ? sk : nullptr,
+                               c->stream));
+    } else {
+      uint32_t* tc[MAXC] = {};
+      for (int j = 0; j < e->arity; ++j) {
+        h->tcols.push_back(std::make_unique<Buf>());
+        XL_TRY(dalloc(c, (size_t)n * 4, h->tcols.back().get(), "tiled index column"));
+        tc[j] = h->tcols.back()->as<uint32_t>();
+        q.col[j] = tc[j];
+      }
+      HIP_TRY(c, k::gather_cols(e->col, tc, e->arity, spm, n, c->stream));
+      if (presorted)  // the whole keys of the rows in their new order
+        HIP_TRY(c, k::tile_keys(q.col[zc], q.col[p.carried_ycol], n, e->lo[zc], h->kp.lo[1], h->tile, h->ntiles,
+                                (uint32_t)zr, false, sk, c->stream));
     }
-    HIP_TRY(c, k::gather_cols(e->col, tc, e->arity, spm, n, c->stream));
-    if (presorted)  // the whole keys of the rows in their new order
-      HIP_TRY(c, k::tile_keys(q.col[zc], q.col[p.carried_ycol], n, e->lo[zc], h->kp.lo[1], h->tile, h->ntiles,
-                              (uint32_t)zr, false, sk, c->stream));
     HIP_TRY(c, k::csr_offsets(sk, n, (uint32_t)nkeys, h->toff.as<uint32_t>(), c->stream));
     return XL_OK;
   }
@@ -3263,6 +3272,8 @@ struct Runner {
     int fcol = 0;
     a.fast = (int8_t)affine_value(p, &fcol);
     a.fcol = (int8_t)fcol;
+    if (a.fast && !h->tcols.empty()) a.pairs = (const uint2*)h->tcols[0]->p;
+    if (a.fast && h->tcols.empty()) a.pairs = (const uint2*)h->toff.p;  // no rows: never read
     a.nops = (int32_t)p.stage_ops[0].size();
     for (int i = 0; i < a.nops; ++i) a.ops[i] = p.stage_ops[0][i];
     for (size_t i = 0; i < p.stage_consts[0].size(); ++i) a.consts[i] = p.stage_consts[0][i];

@@ -244,6 +244,11 @@ size_t dense_tile_lds_bytes(uint32_t tile);
 hipError_t tile_keys(const uint32_t* zc, const uint32_t* yc, int64_t n, int32_t zlo, int32_t lo1, uint32_t tile,
                      uint32_t ntiles, uint32_t zr, bool tile_only, uint32_t* key, hipStream_t s);
 hipError_t dense_min_tiles(const DenseTileArgs& a, hipStream_t s);
+// pairs[i] = (Y of row perm[i] within its tile, wc of that row), and (key
+// given) key[i] = the row's whole key as tile_keys computes it.
+hipError_t tile_pairs(const uint32_t* perm, const uint32_t* zc, const uint32_t* yc, const uint32_t* wc, int64_t n,
+                      int32_t zlo, int32_t lo1, uint32_t tile, uint32_t ntiles, uint32_t zr, void* pairs,
+                      uint32_t* key, hipStream_t s);
 // The same delta rows in one launch after a tile round that wrote tcnt
 // ([n0 * ntiles] improved slots per (rank, tile), DenseTileArgs::tcnt): one
 // workgroup per tile sums the counts of the tiles before it itself.  Fills
