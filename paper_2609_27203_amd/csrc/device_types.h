@@ -221,8 +221,8 @@ struct StageArgs {
 // index order: the result is deterministic.
 struct DensePullArgs {
   const uint32_t* list;   // marked delta slots, ascending
-  int64_t n;              // listed keys, or their upper bound when n_dev is set
-  const uint32_t* n_dev;  // listed keys in device memory (batched rounds), else null
+  uint32_t* mark;         // or (batched rounds) the mark words themselves
+  int64_t n;              // listed keys, or slots covered by the mark words
   const uint32_t* dict;   // rank -> first key value
   uint32_t range1;
   uint32_t nrank;         // ranks (first key values in the dictionary)
@@ -246,7 +246,7 @@ struct DensePullArgs {
   uint32_t* k0;           // next delta rows, row i for list[i] (all null: not written)
   uint32_t* k1;
   uint32_t* v;
-  unsigned long long* counters;  // CNT_INSERTED: keys new to the full relation; CNT_FATAL
+  unsigned long long* counters;  // CNT_INSERTED: keys new to the full relation; CNT_CANDIDATES; CNT_FATAL
 };
 
 // One round of a carried-value rule over a dense min/max head, tiled: the

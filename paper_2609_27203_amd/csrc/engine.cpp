@@ -2783,18 +2783,15 @@ struct Runner {
   // Batched pull rounds: a sum/logsumexp stratum whose one carried-value rule
   // adds or subtracts a column of e (every key with an in-edge from a delta
   // key gets a value, so the marks need no join) enqueues `batched_rounds`
-  // rounds per host read.  Each round marks, lists and pulls with the key
-  // count in device memory (the list holds every slot), writes no delta
-  // rows, and leaves its delta size in a device array; rounds enqueued past
-  // the fixpoint find no marks and change nothing.
+  // rounds per host read.  Each round marks, then pulls straight from the mark
+  // words, writes no delta rows, and leaves its delta size in its counters;
+  // rounds enqueued past the fixpoint find no marks and change nothing.
   bool batched_pull(const Stratum& s) {
     if (c->batched_rounds <= 0 || heads.size() != 1 || !heads[0]->ds || s.variants.size() != 1 ||
         !s.variants[0].driver_delta || head_of(s.variants[0].head) != heads[0].get())
       return false;
     int fcol = 0;
-    if (!affine_value(s.variants[0], &fcol)) return false;
-    const HeadRun* h = heads[0].get();
-    return (double)h->nrank_d * h->range1 * 4 <= (double)c->arena.largest_free() / 2;  // the list
+    return affine_value(s.variants[0], &fcol) != 0;
   }
 
   xl_status run_pull_batched(const RulePlan& p, HeadRun* h, int64_t max_iterations) {
@@ -2805,11 +2802,8 @@ struct Runner {
     IndexProbe fwd{};
     XL_TRY(get_index(sp.rel, sp.key_col, &fwd, -1, nullptr, 0, true));
     const int B = c->batched_rounds;
-    Buf acc, rounds, list;
-    XL_TRY(dalloc(c, 8 * CNT_N, &acc, "round counters"));
-    XL_TRY(dalloc(c, (size_t)B * 4, &rounds, "round delta sizes"));
-    XL_TRY(dalloc(c, (size_t)nsd * 4, &list, "marked keys"));
-    HIP_TRY(c, hipMemsetAsync(acc.p, 0, 8 * CNT_N, c->stream));
+    Buf acc;
+    XL_TRY(dalloc(c, (size_t)B * 8 * CNT_N, &acc, "round counters"));
     std::vector<hipEvent_t> evs;
     if (c->profile) {
       evs.resize(2 * (size_t)B, nullptr);
@@ -2821,6 +2815,7 @@ struct Runner {
       evs.clear();
     };
     int64_t pass = 0, delta = h->dn;
+    u64 fatal = 0;
     xl_status status = XL_OK;
     while (delta > 0 && status == XL_OK) {
       if (pass >= max_iterations) {
@@ -2829,59 +2824,50 @@ struct Runner {
         break;
       }
       const int nb = (int)std::min<int64_t>(B, max_iterations - pass);
-      HIP_TRY(c, hipMemsetAsync(rounds.p, 0, (size_t)nb * 4, c->stream));
+      HIP_TRY(c, hipMemsetAsync(acc.p, 0, (size_t)nb * 8 * CNT_N, c->stream));
       for (int r = 0; r < nb; ++r) {
-        uint32_t* nr = rounds.as<uint32_t>() + r;
         // the mark pass also clears the presence bits this round's pull
         // writes (the round before last's, no longer read)
         HIP_TRY(c, k::dense_mark_out(fwd, p.carried_ycol, h->kp.lo[1], (uint32_t)h->range1, (uint32_t)h->nrank_d,
                                      h->dcur_pres.as<uint32_t>(), h->dchg.as<uint32_t>(),
                                      h->dnext_pres.as<uint32_t>(), c->stream));
-        HIP_TRY(c, k::bits_list_waves(h->dchg.as<uint32_t>(), nsd, list.as<uint32_t>(), nr, c->stream));
         DensePullArgs q{};
         XL_TRY(pull_args(p, h, fast, fcol, q));
-        q.list = list.as<uint32_t>();
+        q.mark = h->dchg.as<uint32_t>();
         q.n = nsd;
-        q.n_dev = nr;
-        q.counters = acc.as<unsigned long long>();
+        q.counters = acc.as<unsigned long long>() + (size_t)r * CNT_N;
         if (c->profile) HIP_TRY(c, hipEventRecord(evs[2 * r], c->stream));
-        HIP_TRY(c, k::dense_pull(q, c->stream));
+        HIP_TRY(c, k::dense_pull_marks(q, c->stream));
         if (c->profile) HIP_TRY(c, hipEventRecord(evs[2 * r + 1], c->stream));
         std::swap(h->dcur.p, h->dnext.p);
         std::swap(h->dcur_pres.p, h->dnext_pres.p);
       }
-      std::vector<uint32_t> n(nb);
-      XL_TRY(ctl_read(c, rounds.p, (size_t)nb * 4, n.data()));
-      int done = nb;
-      for (int r = 0; r < nb; ++r)
-        if (n[r] == 0) {
-          done = r + 1;
-          break;
-        }
-      for (int r = 0; r < done; ++r) {
+      std::vector<u64> cnt((size_t)nb * CNT_N);
+      XL_TRY(ctl_read(c, acc.p, (size_t)nb * 8 * CNT_N, cnt.data()));
+      for (int r = 0; r < nb && delta > 0; ++r) {
+        const u64* cr = cnt.data() + (size_t)r * CNT_N;
+        delta = (int64_t)cr[CNT_APPENDED];
+        fatal |= cr[CNT_FATAL];
         st->iterations++;
-        record(n[r]);
-        st->new_tuples_total += n[r];
+        record(delta);
+        st->new_tuples_total += delta;
+        cands += (int64_t)cr[CNT_CANDIDATES];
+        h->keys += (int64_t)cr[CNT_INSERTED];
         if (c->profile) {
           float ms = 0;
           HIP_TRY(c, hipEventElapsedTime(&ms, evs[2 * r], evs[2 * r + 1]));
           st->pull_ms += ms;
           st->pull_launches++;
-          st->pull_new += n[r];
+          st->pull_new += delta;
+          st->pull_candidates += (int64_t)cr[CNT_CANDIDATES];
         }
+        ++pass;
       }
-      pass += done;
-      delta = n[done - 1];
     }
     destroy_events();
     // the next presence bits are clear between rounds everywhere else
     HIP_TRY(c, k::fill_bytes(h->dnext_pres.p, 0, (size_t)(nsd / 32) * 4, c->stream));
-    u64 tot[CNT_N];
-    XL_TRY(ctl_read(c, acc.p, sizeof(tot), tot));
-    if (tot[CNT_FATAL]) return c->fail(XL_DEVICE_ERROR, "marked key without a contribution (internal)");
-    cands += (int64_t)tot[CNT_CANDIDATES];
-    if (c->profile) st->pull_candidates += (int64_t)tot[CNT_CANDIDATES];
-    h->keys += (int64_t)tot[CNT_INSERTED];
+    if (fatal) return c->fail(XL_DEVICE_ERROR, "marked key without a contribution (internal)");
     h->dn = 0;
     if (status != XL_OK) return status;
     if (h->rel->max_rows > 0 && h->keys > h->rel->max_rows)

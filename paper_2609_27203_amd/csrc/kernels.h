@@ -209,10 +209,13 @@ hipError_t dense_delta_rows(const uint32_t* idx, int64_t n, const uint32_t* vals
 // in two calls on the same temp (write=false counts into *total; write=true
 // writes the list and clears the bits).
 size_t bits_list_temp_bytes(int64_t nbits);
-hipError_t bits_list_waves(uint32_t* bits, int64_t nbits, uint32_t* list, uint32_t* total, hipStream_t s);
 hipError_t bits_list(uint32_t* bits, int64_t nbits, uint32_t* list, uint32_t* total, void* temp, bool write,
                      hipStream_t s);
 hipError_t dense_pull(const DensePullArgs& a, hipStream_t s);
+// The same over the marked slots of a.mark (a.n slots, a multiple of 32; a.fast
+// rules), which it clears; npres must be zero on entry.  CNT_APPENDED counts the
+// marked keys.
+hipError_t dense_pull_marks(const DensePullArgs& a, hipStream_t s);
 // Marks (target-major, nrank a multiple of 32) of the keys that receive a
 // contribution from the delta presence bits pres, pushed through e's index by
 // its Z column (fwd; ycol = e's Y column); mark must be all zero on entry.

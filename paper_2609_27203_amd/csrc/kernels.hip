@@ -2253,77 +2253,6 @@ __global__ __launch_bounds__(MK_THREADS) void bits_list_k(uint32_t* bits, int64_
   }
 }
 
-// Marked slots -> slot list in one pass, clearing the marks: each wavefront
-// takes 128 consecutive words (two per lane, lane-major, so the loads
-// coalesce; a wavefront's word columns go out one after another, so short
-// wavefronts finish sooner); the four wavefronts of a workgroup reserve
-// their entries with one atomic on *total (one per wavefront put thousands
-// of same-address atomics in line) and each writes its entries in word
-// order.  The list is ascending within each wavefront's range and
-// the ranges land in any order: for consumers that take each listed key on
-// its own (the dense pull folds every key's in-edges itself).  Each word
-// column's entries are staged in LDS (entry o at o + o / 32, so the lanes of
-// a nearly full column write different banks) and go out with consecutive
-// lanes on consecutive entries.  *total must be zero before the launch.
-constexpr int LW_WORDS = 2;
-constexpr int LW_STAGE = 64 * 32 + 64;  // one column's entries, padded
-__global__ __launch_bounds__(256) void bits_list_waves_k(uint32_t* bits, int64_t nw, uint32_t* list, uint32_t* total) {
-  __shared__ uint32_t stage_all[4][LW_STAGE];
-  __shared__ uint32_t s_all[4], s_base[4];
-  const int lane = lane_id(), wv = threadIdx.x >> 6;
-  uint32_t* stage = stage_all[wv];
-  // workgroup-uniform steps (the reservation takes two barriers)
-  for (int64_t g0 = (int64_t)blockIdx.x * 4 * 64 * LW_WORDS; g0 < nw; g0 += (int64_t)gridDim.x * 4 * 64 * LW_WORDS) {
-    const int64_t w0 = g0 + (int64_t)wv * 64 * LW_WORDS;
-    uint32_t d[LW_WORDS], run[LW_WORDS], cnt[LW_WORDS], all = 0;
-#pragma unroll
-    for (int k = 0; k < LW_WORDS; ++k) {
-      const int64_t wi = w0 + k * 64 + lane;
-      d[k] = wi < nw ? bits[wi] : 0u;
-      const uint32_t c = (uint32_t)__popc(d[k]);
-      const uint32_t incl = wave_incl_scan(c);
-      run[k] = incl - c;
-      cnt[k] = __shfl(incl, 63, 64);
-      all += cnt[k];
-    }
-    if (lane == 0) s_all[wv] = all;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const uint32_t a0 = s_all[0], a1 = s_all[1], a2 = s_all[2], a3 = s_all[3];
-      const uint32_t sum = a0 + a1 + a2 + a3;
-      const uint32_t b = sum ? atomicAdd(total, sum) : 0u;
-      s_base[0] = b;
-      s_base[1] = b + a0;
-      s_base[2] = b + a0 + a1;
-      s_base[3] = b + a0 + a1 + a2;
-    }
-    __syncthreads();
-    if (all == 0) continue;  // (wave-uniform; the next step's barriers come after s_base is read)
-    uint32_t base = s_base[wv];
-#pragma unroll
-    for (int k = 0; k < LW_WORDS; ++k) {
-      if (cnt[k] == 0) continue;  // (wave-uniform)
-      const int64_t wi = w0 + k * 64 + lane;
-      if (d[k]) {
-        bits[wi] = 0u;
-        uint32_t o = run[k];
-        for (uint32_t b = d[k]; b; b &= b - 1, ++o) stage[o + (o >> 5)] = (uint32_t)wi * 32u + (uint32_t)(__ffs(b) - 1);
-      }
-      wave_lds_sync();
-      for (uint32_t o = (uint32_t)lane; o < cnt[k]; o += 64) list[base + o] = stage[o + (o >> 5)];
-      base += cnt[k];
-      wave_lds_sync();
-    }
-  }
-}
-hipError_t bits_list_waves(uint32_t* bits, int64_t nbits, uint32_t* list, uint32_t* total, hipStream_t s) {
-  const int64_t nw = (nbits + 31) / 32;
-  if (nw <= 0) return hipSuccess;
-  const int64_t waves = (nw + 64 * LW_WORDS - 1) / (64 * LW_WORDS);
-  bits_list_waves_k<<<(unsigned)std::min<int64_t>((waves + 3) / 4, 2048), 256, 0, s>>>(bits, nw, list, total);
-  return hipGetLastError();
-}
-
 // Rows (k0, k1) of the set bits of a dense key bitmap, in bit order: bit b
 // is k0 = lo0 + b / row_bits, k1 = lo1 + b % row_bits (one key: k0 = lo0 + b).
 // Optionally clears the words it read (a delta bitmap).  A workgroup owns
@@ -2539,184 +2468,342 @@ __device__ __forceinline__ T seg_sum_scan(T v, int lane, int head) {
   return v;
 }
 
+// Folds up to eight contributions x[q] = cv[q] + / - wv[q] (those with on[q])
+// into a key's state: (max m, sum of exp(x - m) in facc) for logsumexp, the
+// sum otherwise, in order.  The eight share one rescale of the running sum
+// (nine exponentials without a branch, where one at a time took two per
+// contribution on divergent lanes).
+__device__ __forceinline__ void pull_fold8(int fast, int type, bool lse, const uint32_t (&cv)[8],
+                                           const uint32_t (&wv)[8], const uint32_t (&on)[8], float& m, float& facc,
+                                           uint32_t& uacc) {
+  if (lse) {
+    float x[8], nm = m;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      x[q] = on[q] ? __uint_as_float(fast_value(fast, T_F32, cv[q], wv[q])) : -INFINITY;
+      nm = fmaxf(nm, x[q]);
+    }
+    if (nm == -INFINITY) return;
+    facc = m == nm ? facc : m == -INFINITY ? 0.0f : facc * expf(m - nm);
+    m = nm;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) facc += expf(x[q] - nm);
+    return;
+  }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const uint32_t x = fast_value(fast, type, cv[q], wv[q]);
+    if (type == T_F32) facc = on[q] ? __fadd_rn(facc, __uint_as_float(x)) : facc;
+    else uacc += on[q] ? x : 0u;
+  }
+}
+
+// LDS of one wavefront's segmented walk.
+struct PullLds {
+  uint32_t excl[64], beg[64], key[64], m[64], acc[64], any[64];
+};
+
+// Fold of the contributions of key t (lanes with act) over its in-edges; the
+// lanes of a wavefront together.
+template <bool FAST>
+__device__ __forceinline__ uint32_t pull_fold(PullArgs& a, uint32_t t, bool act, PullLds& L, uint32_t& examined) {
+  const int lane = lane_id();
+  const bool lse = a.fold_kind == FOLD_LSE, f32 = a.val_type == T_F32;
+  uint32_t e0 = 0, deg = 0;
+  if (act) {
+    const uint32_t kk = t / a.nrank + (uint32_t)a.lo1 - (uint32_t)a.rev.key_lo;
+    if (kk < a.rev.key_range) {
+      e0 = a.rev.off[kk];
+      deg = a.rev.off[kk + 1] - e0;
+    }
+  }
+  const uint32_t incl = wave_incl_scan(deg);
+  const uint32_t total = __shfl(incl, 63, 64);
+  if (lane == 0) examined += total;
+  uint32_t maxdeg = deg;
+  for (int k = 32; k > 0; k >>= 1) maxdeg = max(maxdeg, (uint32_t)__shfl_xor(maxdeg, k, 64));
+  if (maxdeg <= DP_LANE_MAX) {
+    // Short lists: one lane per key, every key's j-th in-edge in step j.
+    // Listed keys are ordered by y, so the keys of one y read the delta
+    // values of one z at consecutive slots.  Sequential fold per key in
+    // index order (online max shift for logsumexp).
+    const uint32_t r = t % a.nrank, y = t / a.nrank + (uint32_t)a.lo1;
+    float m = -INFINITY, facc = 0.0f;
+    uint32_t uacc = 0;
+    bool any = false;
+    auto fold = [&](uint32_t x) {
+      any = true;
+      if (lse) {
+        const float xv = __uint_as_float(x);
+        if (xv > m) {
+          facc = (m == -INFINITY ? 0.0f : facc * expf(m - xv)) + 1.0f;
+          m = xv;
+        } else if (xv != -INFINITY) {
+          facc += expf(xv - m);
+        }
+      } else if (f32) {
+        facc = __fadd_rn(facc, __uint_as_float(x));
+      } else {
+        uacc += x;
+      }
+    };
+    if constexpr (FAST) {
+      // the value is one add/subtract of the delta value and a column of
+      // e: eight in-edges at a time, each level of loads issued together
+      const uint32_t* zc = a.rev.col[a.zcol];
+      const uint32_t* wc = a.rev.col[a.fcol];
+      for (uint32_t jb = 0; jb < maxdeg; jb += 8) {
+        uint32_t zs[8], wv[8], pw[8], cv[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const uint32_t jj = jb + (uint32_t)q;
+          const uint32_t zb = jj < deg ? zc[e0 + jj] - (uint32_t)a.lo1 : 0xffffffffu;
+          zs[q] = zb < a.range1 ? zb * a.nrank + r : 0xffffffffu;
+          wv[q] = jj < deg ? wc[e0 + jj] : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) pw[q] = zs[q] != 0xffffffffu ? a.cpres[zs[q] >> 5] : 0u;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const bool pres = zs[q] != 0xffffffffu && ((pw[q] >> (zs[q] & 31)) & 1u);
+          cv[q] = pres ? a.cval[zs[q]] : 0u;
+          pw[q] = pres;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) any = any || pw[q];
+        pull_fold8(a.fast, a.val_type, lse, cv, wv, pw, m, facc, uacc);
+      }
+    }
+    for (uint32_t jj = 0; !FAST && jj < maxdeg; ++jj) {
+      if (jj >= deg) continue;
+      Regs u;
+      if (!pull_bind<FAST>(a, r, a.dict[r], y, e0 + jj, u)) continue;
+      const uint32_t x = getv(u, a.val_slot);
+      any = true;
+      if (lse) {
+        const float xv = __uint_as_float(x);
+        if (xv > m) {
+          facc = (m == -INFINITY ? 0.0f : facc * expf(m - xv)) + 1.0f;
+          m = xv;
+        } else if (xv != -INFINITY) {
+          facc += expf(xv - m);
+        }
+      } else if (f32) {
+        facc = __fadd_rn(facc, __uint_as_float(x));
+      } else {
+        uacc += x;
+      }
+    }
+    if (act && !any) atomicOr(&a.counters[CNT_FATAL], 8ull);  // a marked key always has a contribution
+    if (lse) return __float_as_uint(m == -INFINITY ? -INFINITY : m + logf(facc));
+    return f32 ? __float_as_uint(facc) : uacc;
+  }
+  L.excl[lane] = incl - deg;
+  L.beg[lane] = e0;
+  L.key[lane] = t;
+  L.m[lane] = __float_as_uint(-INFINITY);
+  L.acc[lane] = 0u;
+  L.any[lane] = 0u;
+  wave_lds_sync();
+  for (uint32_t base = 0; base < total; base += 64) {
+    const uint32_t j = base + (uint32_t)lane;
+    const bool on = j < total;
+    int q = 0;
+#pragma unroll
+    for (int step = 32; step > 0; step >>= 1)
+      if (L.excl[q + step] <= j) q += step;
+    bool ok = false;
+    uint32_t x = 0;
+    if (on) {
+      const uint32_t tq = L.key[q], r = tq % a.nrank;
+      Regs u;
+      ok = pull_bind<FAST>(a, r, a.dict[r], tq / a.nrank + (uint32_t)a.lo1, L.beg[q] + (j - L.excl[q]), u);
+      if (ok) x = getv(u, a.val_slot);
+    }
+    // runs of equal owners among the active lanes
+    const int qp = __shfl_up(q, 1, 64);
+    const u64 am = __ballot(on);
+    const u64 heads = __ballot(on && (lane == 0 || qp != q)) | ~am;
+    const int head = 63 - __clzll((long long)(heads & ((2ull << lane) - 1ull)));
+    const u64 above = heads & ~((2ull << lane) - 1ull);
+    const int tail = above ? __ffsll((long long)above) - 2 : 63;
+    const bool is_tail = on && tail == lane;
+    const int oks = seg_sum_scan<int>(ok ? 1 : 0, lane, head);
+    if (lse) {
+      const float xv = ok ? __uint_as_float(x) : -INFINITY;
+      const float mrun = __shfl(seg_max_scan(xv, lane, head), tail, 64);
+      const float ev = (ok && mrun != -INFINITY) ? expf(xv - mrun) : 0.0f;
+      const float srun = seg_sum_scan<float>(ev, lane, head);
+      if (is_tail && oks > 0) {
+        const float m = __uint_as_float(L.m[q]), acc = __uint_as_float(L.acc[q]);
+        float nm = m, nacc = acc;
+        if (mrun != -INFINITY) {
+          if (mrun > m) {
+            nacc = (m == -INFINITY ? 0.0f : acc * expf(m - mrun)) + srun;
+            nm = mrun;
+          } else {
+            nacc = acc + srun * expf(mrun - m);
+          }
+        }
+        L.m[q] = __float_as_uint(nm);
+        L.acc[q] = __float_as_uint(nacc);
+        L.any[q] = 1u;
+      }
+    } else if (f32) {
+      const float srun = seg_sum_scan<float>(ok ? __uint_as_float(x) : 0.0f, lane, head);
+      if (is_tail && oks > 0) {
+        L.acc[q] = __float_as_uint(__fadd_rn(__uint_as_float(L.acc[q]), srun));
+        L.any[q] = 1u;
+      }
+    } else {
+      const uint32_t srun = seg_sum_scan<uint32_t>(ok ? x : 0u, lane, head);
+      if (is_tail && oks > 0) {
+        L.acc[q] += srun;
+        L.any[q] = 1u;
+      }
+    }
+    wave_lds_sync();
+  }
+  if (act && !L.any[lane]) atomicOr(&a.counters[CNT_FATAL], 8ull);
+  uint32_t out = L.acc[lane];
+  if (lse) {
+    const float m = __uint_as_float(L.m[lane]);
+    out = __float_as_uint(m == -INFINITY ? -INFINITY : m + logf(__uint_as_float(L.acc[lane])));
+  }
+  wave_lds_sync();
+  return out;
+}
+
+// pull_fold for P x 64 consecutive slots t0 + 64p + lane of one target (t0 and
+// nrank multiples of 64; act[p]: marked): the in-edges, and for each of them
+// the presence bits, are the same for all lanes, so they come through scalar
+// loads (none of these arrays is written by this launch) and only the delta
+// values are vector loads, 64 consecutive words each, 8P of them in flight.
+// False when the target has more than DP_LANE_MAX in-edges (nothing is folded
+// then).
+typedef XL_KARG const uint32_t* UniformPtr;
+template <int P>
+__device__ __forceinline__ bool pull_fold_row(PullArgs& a, uint32_t t0, const bool (&act)[P], uint32_t (&out)[P],
+                                              uint32_t& examined) {
+  const int lane = lane_id();
+  const bool lse = a.fold_kind == FOLD_LSE, f32 = a.val_type == T_F32;
+  const uint32_t y = t0 / a.nrank, r0 = t0 - y * a.nrank;
+  const uint32_t kk = y + (uint32_t)a.lo1 - (uint32_t)a.rev.key_lo;
+  uint32_t e0 = 0, deg = 0;
+  if (kk < a.rev.key_range) {
+    UniformPtr off = (UniformPtr)(uintptr_t)a.rev.off;
+    e0 = off[kk];
+    deg = off[kk + 1] - e0;
+  }
+  if (deg > DP_LANE_MAX) return false;
+  UniformPtr zc = (UniformPtr)(uintptr_t)(a.rev.col[a.zcol] + e0), wc = (UniformPtr)(uintptr_t)(a.rev.col[a.fcol] + e0);
+  UniformPtr cpres = (UniformPtr)(uintptr_t)a.cpres;
+  const uint32_t* cval = a.cval + lane;
+  float m[P], facc[P];
+  uint32_t uacc[P];
+  bool any[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const uint32_t keys = (uint32_t)__popcll(__ballot(act[p]));
+    if (lane == 0) examined += deg * keys;
+    m[p] = -INFINITY;
+    facc[p] = 0.0f;
+    uacc[p] = 0;
+    any[p] = false;
+  }
+  for (uint32_t jb = 0; jb < deg; jb += 8) {
+    uint32_t zs[8], wv[8], cv[P][8], on[P][8];
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q) {
+      const uint32_t jj = min(jb + q, deg - 1);
+      const uint32_t zb = zc[jj] - (uint32_t)a.lo1;
+      wv[q] = wc[jj];
+      zs[q] = jb + q < deg && zb < a.range1 ? zb * a.nrank + r0 : 0xffffffffu;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q) {
+      const bool in = zs[q] != 0xffffffffu;
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        u64 mask = 0;
+        if (in) mask = (u64)cpres[(zs[q] >> 5) + 2 * p] | ((u64)cpres[(zs[q] >> 5) + 2 * p + 1] << 32);
+        on[p][q] = (uint32_t)((mask >> lane) & 1ull);
+      }
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q)
+#pragma unroll
+      for (int p = 0; p < P; ++p) cv[p][q] = on[p][q] ? cval[zs[q] + 64u * p] : 0u;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+#pragma unroll
+      for (uint32_t q = 0; q < 8; ++q) any[p] = any[p] || on[p][q];
+      pull_fold8(a.fast, a.val_type, lse, cv[p], wv, on[p], m[p], facc[p], uacc[p]);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    if (act[p] && !any[p]) atomicOr(&a.counters[CNT_FATAL], 8ull);
+    out[p] = lse ? __float_as_uint(m[p] == -INFINITY ? -INFINITY : m[p] + logf(facc[p]))
+                 : f32 ? __float_as_uint(facc[p]) : uacc[p];
+  }
+  return true;
+}
+
+// The full relation's value of a key with contribution out (cur: its value
+// before, had: whether it had one).
+__device__ __forceinline__ uint32_t pull_merge(uint32_t cur, uint32_t out, bool had, bool lse, bool f32) {
+  if (!had) return out;
+  if (lse) return __float_as_uint(lse2(__uint_as_float(cur), __uint_as_float(out)));
+  if (f32) return __float_as_uint(__fadd_rn(__uint_as_float(cur), __uint_as_float(out)));
+  return cur + out;
+}
+
+// A workgroup's counts (the sums of 32-bit counts may pass 2^32).
+template <int WAVES>
+__device__ __forceinline__ void pull_counts(u64* counters, uint32_t keys, uint32_t ins, uint32_t examined) {
+  __shared__ u64 s_t[3][WAVES];
+  const int lane = lane_id(), w = threadIdx.x >> 6;
+  u64 tk = keys, ti = ins, te = examined;
+  for (int k = 32; k > 0; k >>= 1) {
+    tk += __shfl_xor(tk, k, 64);
+    ti += __shfl_xor(ti, k, 64);
+    te += __shfl_xor(te, k, 64);
+  }
+  if (lane == 0) {
+    s_t[0][w] = tk;
+    s_t[1][w] = ti;
+    s_t[2][w] = te;
+  }
+  __syncthreads();
+  if (w == 0) {
+    tk = ti = te = 0;
+    for (int k = 0; k < WAVES; ++k) {
+      tk += s_t[0][k];
+      ti += s_t[1][k];
+      te += s_t[2][k];
+    }
+    wave_counters_add(counters, tk, ti, te);
+  }
+}
+
+// Keys from a list (rounds one at a time, and rules of any value).
 template <bool FAST>
 __global__ __launch_bounds__(DP_WAVES * 64) void dense_pull_k(DensePullArgs by_value) {
   (void)by_value;
   PullArgs& a = *(PullArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-  __shared__ uint32_t s_excl[DP_WAVES][64], s_beg[DP_WAVES][64], s_key[DP_WAVES][64];
-  __shared__ uint32_t s_m[DP_WAVES][64], s_acc[DP_WAVES][64], s_any[DP_WAVES][64];
+  __shared__ PullLds s_l[DP_WAVES];
   const int lane = lane_id(), w = threadIdx.x >> 6;
   const bool lse = a.fold_kind == FOLD_LSE, f32 = a.val_type == T_F32;
-  const int64_t nkeys = a.n_dev ? (int64_t)*a.n_dev : a.n;
+  const int64_t nkeys = a.n;
   const int64_t nchunks = (nkeys + 63) / 64;
   uint32_t mine = 0, examined = 0;
   for (int64_t chunk = (int64_t)blockIdx.x * DP_WAVES + w; chunk < nchunks; chunk += (int64_t)gridDim.x * DP_WAVES) {
     const int64_t i = chunk * 64 + lane;
-    uint32_t t = 0, e0 = 0, deg = 0;
-    if (i < nkeys) {
-      t = a.list[i];
-      const uint32_t kk = t / a.nrank + (uint32_t)a.lo1 - (uint32_t)a.rev.key_lo;
-      if (kk < a.rev.key_range) {
-        e0 = a.rev.off[kk];
-        deg = a.rev.off[kk + 1] - e0;
-      }
-    }
-    const uint32_t incl = wave_incl_scan(deg);
-    const uint32_t total = __shfl(incl, 63, 64);
-    if (lane == 0) examined += total;
-    s_excl[w][lane] = incl - deg;
-    s_beg[w][lane] = e0;
-    s_key[w][lane] = t;
-    s_m[w][lane] = __float_as_uint(-INFINITY);
-    s_acc[w][lane] = 0u;
-    s_any[w][lane] = 0u;
-    wave_lds_sync();
-    uint32_t maxdeg = deg;
-    for (int k = 32; k > 0; k >>= 1) maxdeg = max(maxdeg, (uint32_t)__shfl_xor(maxdeg, k, 64));
-    if (maxdeg <= DP_LANE_MAX) {
-      // Short lists: one lane per key, every key's j-th in-edge in step j.
-      // Listed keys are ordered by y, so the keys of one y read the delta
-      // values of one z at consecutive slots.  Sequential fold per key in
-      // index order (online max shift for logsumexp).
-      const uint32_t r = t % a.nrank, y = t / a.nrank + (uint32_t)a.lo1;
-      float m = -INFINITY, facc = 0.0f;
-      uint32_t uacc = 0;
-      bool any = false;
-      auto fold = [&](uint32_t x) {
-        any = true;
-        if (lse) {
-          const float xv = __uint_as_float(x);
-          if (xv > m) {
-            facc = (m == -INFINITY ? 0.0f : facc * expf(m - xv)) + 1.0f;
-            m = xv;
-          } else if (xv != -INFINITY) {
-            facc += expf(xv - m);
-          }
-        } else if (f32) {
-          facc = __fadd_rn(facc, __uint_as_float(x));
-        } else {
-          uacc += x;
-        }
-      };
-      if constexpr (FAST) {
-        // the value is one add/subtract of the delta value and a column of
-        // e: eight in-edges at a time, each level of loads issued together
-        const uint32_t* zc = a.rev.col[a.zcol];
-        const uint32_t* wc = a.rev.col[a.fcol];
-        for (uint32_t jb = 0; jb < maxdeg; jb += 8) {
-          uint32_t zs[8], wv[8], pw[8], cv[8];
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const uint32_t jj = jb + (uint32_t)q;
-            const uint32_t zb = jj < deg ? zc[e0 + jj] - (uint32_t)a.lo1 : 0xffffffffu;
-            zs[q] = zb < a.range1 ? zb * a.nrank + r : 0xffffffffu;
-            wv[q] = jj < deg ? wc[e0 + jj] : 0u;
-          }
-#pragma unroll
-          for (int q = 0; q < 8; ++q) pw[q] = zs[q] != 0xffffffffu ? a.cpres[zs[q] >> 5] : 0u;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const bool pres = zs[q] != 0xffffffffu && ((pw[q] >> (zs[q] & 31)) & 1u);
-            cv[q] = pres ? a.cval[zs[q]] : 0u;
-            pw[q] = pres;
-          }
-#pragma unroll
-          for (int q = 0; q < 8; ++q)
-            if (pw[q]) fold(fast_value(a.fast, a.val_type, cv[q], wv[q]));
-        }
-      }
-      for (uint32_t jj = 0; !FAST && jj < maxdeg; ++jj) {
-        if (jj >= deg) continue;
-        Regs u;
-        if (!pull_bind<FAST>(a, r, a.dict[r], y, e0 + jj, u)) continue;
-        const uint32_t x = getv(u, a.val_slot);
-        any = true;
-        if (lse) {
-          const float xv = __uint_as_float(x);
-          if (xv > m) {
-            facc = (m == -INFINITY ? 0.0f : facc * expf(m - xv)) + 1.0f;
-            m = xv;
-          } else if (xv != -INFINITY) {
-            facc += expf(xv - m);
-          }
-        } else if (f32) {
-          facc = __fadd_rn(facc, __uint_as_float(x));
-        } else {
-          uacc += x;
-        }
-      }
-      s_m[w][lane] = __float_as_uint(m);
-      s_acc[w][lane] = (lse || f32) ? __float_as_uint(facc) : uacc;
-      s_any[w][lane] = any ? 1u : 0u;
-    }
-    for (uint32_t base = 0; maxdeg > DP_LANE_MAX && base < total; base += 64) {
-      const uint32_t j = base + (uint32_t)lane;
-      const bool act = j < total;
-      int q = 0;
-#pragma unroll
-      for (int step = 32; step > 0; step >>= 1)
-        if (s_excl[w][q + step] <= j) q += step;
-      bool ok = false;
-      uint32_t x = 0;
-      if (act) {
-        const uint32_t tq = s_key[w][q], r = tq % a.nrank;
-        Regs u;
-        ok = pull_bind<FAST>(a, r, a.dict[r], tq / a.nrank + (uint32_t)a.lo1, s_beg[w][q] + (j - s_excl[w][q]), u);
-        if (ok) x = getv(u, a.val_slot);
-      }
-      // runs of equal owners among the active lanes
-      const int qp = __shfl_up(q, 1, 64);
-      const u64 am = __ballot(act);
-      const u64 heads = __ballot(act && (lane == 0 || qp != q)) | ~am;
-      const int head = 63 - __clzll((long long)(heads & ((2ull << lane) - 1ull)));
-      const u64 above = heads & ~((2ull << lane) - 1ull);
-      const int tail = above ? __ffsll((long long)above) - 2 : 63;
-      const bool is_tail = act && tail == lane;
-      const int oks = seg_sum_scan<int>(ok ? 1 : 0, lane, head);
-      if (lse) {
-        const float xv = ok ? __uint_as_float(x) : -INFINITY;
-        const float mrun = __shfl(seg_max_scan(xv, lane, head), tail, 64);
-        const float ev = (ok && mrun != -INFINITY) ? expf(xv - mrun) : 0.0f;
-        const float srun = seg_sum_scan<float>(ev, lane, head);
-        if (is_tail && oks > 0) {
-          const float m = __uint_as_float(s_m[w][q]), acc = __uint_as_float(s_acc[w][q]);
-          float nm = m, nacc = acc;
-          if (mrun != -INFINITY) {
-            if (mrun > m) {
-              nacc = (m == -INFINITY ? 0.0f : acc * expf(m - mrun)) + srun;
-              nm = mrun;
-            } else {
-              nacc = acc + srun * expf(mrun - m);
-            }
-          }
-          s_m[w][q] = __float_as_uint(nm);
-          s_acc[w][q] = __float_as_uint(nacc);
-          s_any[w][q] = 1u;
-        }
-      } else if (f32) {
-        const float srun = seg_sum_scan<float>(ok ? __uint_as_float(x) : 0.0f, lane, head);
-        if (is_tail && oks > 0) {
-          s_acc[w][q] = __float_as_uint(__fadd_rn(__uint_as_float(s_acc[w][q]), srun));
-          s_any[w][q] = 1u;
-        }
-      } else {
-        const uint32_t srun = seg_sum_scan<uint32_t>(ok ? x : 0u, lane, head);
-        if (is_tail && oks > 0) {
-          s_acc[w][q] += srun;
-          s_any[w][q] = 1u;
-        }
-      }
-      wave_lds_sync();
-    }
-    uint32_t out = 0;
-    if (i < nkeys) {
-      if (lse) {
-        const float m = __uint_as_float(s_m[w][lane]);
-        out = __float_as_uint(m == -INFINITY ? -INFINITY : m + logf(__uint_as_float(s_acc[w][lane])));
-      } else {
-        out = s_acc[w][lane];
-      }
-      if (!s_any[w][lane]) atomicOr(&a.counters[CNT_FATAL], 8ull);  // a marked key always has a contribution
+    const bool act = i < nkeys;
+    const uint32_t t = act ? a.list[i] : 0u;
+    const uint32_t out = pull_fold<FAST>(a, t, act, s_l[w], examined);
+    if (act) {
       if (a.k0) {
         const uint32_t r = t % a.nrank, yb = t / a.nrank;
         a.k0[i] = a.dict[r];
@@ -2732,7 +2819,6 @@ __global__ __launch_bounds__(DP_WAVES * 64) void dense_pull_k(DensePullArgs by_v
     // whether its slot was present.  The full relation's value is then read
     // and written by its own lane (each slot is listed once).
     {
-      const bool act = i < nkeys;
       const uint32_t wd = act ? t >> 5 : 0xffffffffu;
       const uint32_t bit = act ? 1u << (t & 31) : 0u;
       const uint32_t wprev = __shfl_up(wd, 1, 64);
@@ -2754,40 +2840,150 @@ __global__ __launch_bounds__(DP_WAVES * 64) void dense_pull_k(DensePullArgs by_v
       old = __shfl(old, tail, 64);
       if (act) {
         const bool had = old & bit;
-        uint32_t nv = out;
-        if (had) {
-          const uint32_t cur = a.fval[t];
-          if (lse) nv = __float_as_uint(lse2(__uint_as_float(cur), __uint_as_float(out)));
-          else if (f32) nv = __float_as_uint(__fadd_rn(__uint_as_float(cur), __uint_as_float(out)));
-          else nv = cur + out;
+        a.fval[t] = pull_merge(had ? a.fval[t] : 0u, out, had, lse, f32);
+        mine += had ? 0u : 1u;
+      }
+    }
+  }
+  pull_counts<DP_WAVES>(a.counters, 0, mine, examined);
+}
+
+// Keys straight from the mark words (batched rounds of a one-add rule).  A
+// unit is eight consecutive words, whose presence its wavefront owns: the next
+// delta's words are the marks themselves and the full relation's take them in
+// with plain stores (every marked key gets a value), and the marks are
+// cleared.  64 marked slots at a time go to the fold: a full pair of words as
+// it is, sparser ones through a queue in LDS, so lanes stay busy whatever the
+// density.  No list is written and read and no presence atomic is needed.
+// A round's marks may lie close together (the layers of a DAG: 40,000 of
+// 800,000 words), so units are small and go round the wavefronts; one load
+// fetches a wavefront's next eight units, since most of them are empty (units
+// of 32 words: 95 us a launch, the work on a quarter of the wavefronts).
+// Bound by the chain in-edge -> delta presence -> delta value at four
+// wavefronts per SIMD, two slots per lane in flight (one slot at five: 797 us
+// per run).  256 sources x 100,000 targets, eight in-edges each,
+// per run of 20 launches: 1015 us (833 of them the pull, the rest the listing)
+// -> 764.
+constexpr int PM_WAVES = 4, PM_WORDS = 8;
+__global__ __launch_bounds__(PM_WAVES * 64, 4) void dense_pull_marks_k(DensePullArgs by_value) {
+  (void)by_value;
+  PullArgs& a = *(PullArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  __shared__ PullLds s_l[PM_WAVES];
+  __shared__ uint32_t s_q[PM_WAVES][128];
+  __shared__ uint8_t s_had[PM_WAVES][128];
+  const int lane = lane_id(), w = threadIdx.x >> 6;
+  const bool lse = a.fold_kind == FOLD_LSE, f32 = a.val_type == T_F32;
+  uint32_t* queue = s_q[w];
+  uint8_t* qhad = s_had[w];
+  uint32_t keys = 0, mine = 0, examined = 0;
+  const uint32_t nw = (uint32_t)(a.n / 32);
+  const uint32_t waves = gridDim.x * PM_WAVES, me = blockIdx.x * PM_WAVES + (uint32_t)w;
+  const uint32_t units = (nw + PM_WORDS - 1) / PM_WORDS;
+  for (uint32_t u0 = me; u0 < units; u0 += 8 * waves) {  // (units < 2^24, waves < 2^16)
+    // lane l holds word l & 7 of unit u0 + (l >> 3) * waves
+    const uint32_t wi = (u0 + (uint32_t)(lane >> 3) * waves) * PM_WORDS + (uint32_t)(lane & 7);
+    const uint32_t word = wi < nw ? a.mark[wi] : 0u;
+    if (!__ballot(word != 0)) continue;
+    uint32_t old = 0;
+    if (word) {
+      old = a.fpres[wi];
+      a.mark[wi] = 0u;
+      a.npres[wi] = word;
+      a.fpres[wi] = old | word;
+      keys += (uint32_t)__popc(word);
+    }
+    uint32_t qn = 0;  // queued slots (uniform)
+    for (int pr = 0; pr <= 32; ++pr) {
+      uint32_t t = 0;
+      bool act = true, had = false;
+      if (pr < 32) {
+        const uint32_t mw = (uint32_t)__shfl((int)word, 2 * pr + (lane >> 5), 64);
+        const bool on = (mw >> (lane & 31)) & 1u;
+        const u64 m = __ballot(on);
+        if (!m) continue;
+        had = ((uint32_t)__shfl((int)old, 2 * pr + (lane >> 5), 64) >> (lane & 31)) & 1u;
+        t = (uint32_t)__shfl((int)wi, 2 * pr, 64) * 32u + (uint32_t)lane;
+        // half full or more: the slots of one target as they are, two pairs of
+        // words at once where the next pair is too
+        if (a.nrank % 64 == 0 && __popcll(m) >= 32) {
+          const uint32_t t0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t - (uint32_t)lane));
+          bool two = false;
+          if (!(pr & 1) && t0 % a.nrank + 64 < a.nrank) {
+            const uint32_t mw2 = (uint32_t)__shfl((int)word, 2 * pr + 2 + (lane >> 5), 64);
+            const bool on2[2] = {on, ((mw2 >> (lane & 31)) & 1u) != 0};
+            if (__popcll(__ballot(on2[1])) >= 32) {
+              const bool had2 = ((uint32_t)__shfl((int)old, 2 * pr + 2 + (lane >> 5), 64) >> (lane & 31)) & 1u;
+              const uint32_t c0 = on && had ? a.fval[t] : 0u, c1 = on2[1] && had2 ? a.fval[t + 64] : 0u;
+              uint32_t out2[2];
+              two = pull_fold_row<2>(a, t0, on2, out2, examined);
+              if (two) {
+                if (on) {
+                  a.nval[t] = out2[0];
+                  a.fval[t] = pull_merge(c0, out2[0], had, lse, f32);
+                  mine += had ? 0u : 1u;
+                }
+                if (on2[1]) {
+                  a.nval[t + 64] = out2[1];
+                  a.fval[t + 64] = pull_merge(c1, out2[1], had2, lse, f32);
+                  mine += had2 ? 0u : 1u;
+                }
+              }
+            }
+          }
+          if (two) {
+            ++pr;
+            continue;
+          }
+          const bool on1[1] = {on};
+          const uint32_t now = on && had ? a.fval[t] : 0u;
+          uint32_t out[1];
+          if (pull_fold_row<1>(a, t0, on1, out, examined)) {
+            if (on) {
+              a.nval[t] = out[0];
+              a.fval[t] = pull_merge(now, out[0], had, lse, f32);
+              mine += had ? 0u : 1u;
+            }
+            continue;
+          }
         }
-        a.fval[t] = nv;
+        if (qn != 0 || ~m != 0) {
+          if (on) {
+            const uint32_t at = qn + (uint32_t)__popcll(m & lanemask_lt());
+            queue[at] = t;
+            qhad[at] = had;
+          }
+          qn += (uint32_t)__popcll(m);
+          wave_lds_sync();
+          if (qn < 64) continue;
+          t = queue[lane];
+          had = qhad[lane];
+          const uint32_t rest = queue[64 + lane];
+          const uint8_t rest_had = qhad[64 + lane];
+          wave_lds_sync();
+          qn -= 64;
+          if ((uint32_t)lane < qn) {
+            queue[lane] = rest;
+            qhad[lane] = rest_had;
+          }
+          wave_lds_sync();
+        }
+      } else {
+        if (qn == 0) continue;
+        act = (uint32_t)lane < qn;
+        t = act ? queue[lane] : 0u;
+        had = act && qhad[lane];
+      }
+      const uint32_t cur = had ? a.fval[t] : 0u;
+      const uint32_t out = pull_fold<true>(a, t, act, s_l[w], examined);
+      if (act) {
+        a.nval[t] = out;
+        a.fval[t] = pull_merge(cur, out, had, lse, f32);
         mine += had ? 0u : 1u;
       }
     }
     wave_lds_sync();
   }
-  // (the sums of 32-bit counts may pass 2^32 over a workgroup)
-  u64 ti = mine, te = examined;
-  for (int k = 32; k > 0; k >>= 1) {
-    ti += __shfl_xor(ti, k, 64);
-    te += __shfl_xor(te, k, 64);
-  }
-  __shared__ u64 s_t[2][DP_WAVES];
-  if (lane == 0) {
-    s_t[0][w] = ti;
-    s_t[1][w] = te;
-  }
-  __syncthreads();
-  if (w == 0) {
-    ti = te = 0;
-#pragma unroll
-    for (int k = 0; k < DP_WAVES; ++k) {
-      ti += s_t[0][k];
-      te += s_t[1][k];
-    }
-    wave_counters_add(a.counters, 0, ti, te);
-  }
+  pull_counts<PM_WAVES>(a.counters, keys, mine, examined);
 }
 
 // At most as many workgroups as the device keeps resident: each wavefront
@@ -2799,6 +2995,16 @@ static hipError_t dense_pull_launch(const DensePullArgs& a, hipStream_t s) {
   hipError_t e = resident_blocks(dense_pull_k<FAST>, DP_WAVES * 64, 0, &cap);
   if (e != hipSuccess) return e;
   dense_pull_k<FAST><<<grid_for((a.n + 63) / 64, DP_WAVES, cap), DP_WAVES * 64, 0, s>>>(a);
+  return hipGetLastError();
+}
+
+hipError_t dense_pull_marks(const DensePullArgs& a, hipStream_t s) {
+  if (a.n <= 0) return hipSuccess;
+  if (!a.fast || !a.mark || a.n % 32 || a.n > (int64_t)0xffffffffll) return hipErrorInvalidValue;
+  int cap = 0;
+  const hipError_t e = resident_blocks(dense_pull_marks_k, PM_WAVES * 64, 0, &cap);
+  if (e != hipSuccess) return e;
+  dense_pull_marks_k<<<grid_for(a.n / 32, PM_WAVES * PM_WORDS, cap), PM_WAVES * 64, 0, s>>>(a);
   return hipGetLastError();
 }
 

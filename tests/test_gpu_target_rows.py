@@ -31,3 +31,38 @@ def test_rows_match_the_hashed_form(layers, width, degree, sources):
     assert np.all(key[1:] > key[:-1])
     for g, w in zip(rels["npaths"], hashed["npaths"]):
         assert np.array_equal(g, w)
+
+
+@pytest.mark.parametrize("width,degree,sources", [(1, 1, 1), (33, 33, 40), (70, 70, 65), (300, 41, 7), (700, 3, 100)])
+def test_pulled_marks_match_a_host_sum(width, degree, sources):
+    """logsumexp rounds that pull straight from the mark words: in-degrees past
+    a step of 32, words with few marks (queued) and full ones, targets across
+    words.  A layer's fold of n terms in 32 bits is off by at most n + 8
+    roundings (exp, log and rescale counted as eight), and the carried value
+    by one of its own per layer."""
+    rng = np.random.default_rng(width * degree)
+    layers, degree = 3, min(degree, width)
+    to = np.stack([rng.choice(width, size=degree, replace=False) for _ in range(layers * width)])
+    src = np.repeat(np.arange(layers * width), degree)
+    dst = to.reshape(-1) + (src // width + 1) * width
+    w = -rng.random(src.size).astype(np.float32)
+    srcs = np.sort(rng.choice(layers * width, size=sources % width + 1, replace=False)).astype(np.int32)
+    wl = W.Workload("lse", W.LSE_RULES, {
+        "edge": (("i32", "i32", "f32"), [src.astype(np.int32), dst.astype(np.int32), w]),
+        "source": (("i32",), [srcs])}, {"score": ("i32", "i32", "f32")})
+    print(f"case: pulled marks width {width} degree {degree} sources {len(srcs)}", flush=True)
+    rels, _, _ = engine_run(wl, workspace_bytes=2 << 30)
+    total = np.zeros((len(srcs), (layers + 1) * width))  # sums of path products
+    prod = np.exp(w.astype(np.float64))
+    for i, s in enumerate(srcs):
+        total[i, s] = 1.0
+        for l in range(s // width, layers):
+            e = slice(l * width * degree, (l + 1) * width * degree)
+            np.add.at(total[i], dst[e], total[i, src[e]] * prod[e])
+        total[i, s] = 0.0
+    at, y = np.nonzero(total)
+    want = np.log(total[at, y])
+    got = rels["score"]
+    assert np.array_equal(got[0], srcs[at]) and np.array_equal(got[1], y)
+    bound = layers * (degree + 8 + np.abs(want).max()) * 2.0**-24
+    assert np.abs(got[2] - want).max() <= bound
