@@ -340,7 +340,7 @@ struct FrontierArgs {
 // only read (rows are shared by all X of one A) and cleared by
 // clear_flagged_rows after the round.
 struct GatherArgs {
-  uint32_t* in_bits;        // [range0][row_words] this round's delta (by_a: emptied as read)
+  uint32_t* in_bits;        // [range0][row_words] this round's delta (by_a: overwritten)
   uint32_t* in_flag;        // [range0]
   uint32_t* out_bits;       // [range0][row_words] next delta (zero on entry)
   uint32_t* out_flag;       // [range0] (zero on entry)
@@ -354,15 +354,17 @@ struct GatherArgs {
   uint32_t row_words;
   int64_t range0;
   unsigned long long* counters;  // CNT_CANDIDATES, CNT_APPENDED
-  // by_a: one workgroup per flagged delta row A instead of per head row X;
-  // e1a is e1 indexed by its A column, e1_xcol the column holding X.  Every
-  // delta row r keeps word bounds: its bits lie in words [lo[r], hi[r])
-  // (empty: lo = row_words, hi = 0); the next round's bounds only widen.
-  // The by_a kernel also empties each delta row it reads (its nonzero words,
-  // its flag and its bounds), so no clearing pass follows the round.
+  // by_a: the union of each flagged delta row A is made once (over the delta
+  // row), then ORed into the head rows; e1a is e1 indexed by its A column,
+  // e1_xcol the column holding X.  Every delta row r keeps word bounds: its
+  // bits lie in words [lo[r], hi[r]) (empty: lo >= hi), other words of a
+  // flagged row and all words of the others are undefined.  With *hubs set, or
+  // without hubs, the unions are ORed by atomics: delta rows are then emptied as they are read
+  // (the nonzero words, the flag and the bounds), and bounds only widen.
   int32_t by_a;
   IndexProbe e1a;
   int32_t e1_xcol;
+  const uint32_t* hubs;     // nonzero: some X has a long list of A values (null: one launch a round)
   uint32_t* in_lo;
   uint32_t* in_hi;
   uint32_t* out_lo;

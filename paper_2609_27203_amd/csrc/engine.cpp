@@ -907,6 +907,7 @@ struct HeadRun {
   bool gather_ready = false;
   Buf gbits, gflag[2];
   Buf gbound[2];  // word bounds of the delta rows of dbits / gbits: lo[range0] then hi[range0]
+  Buf ghubs;      // nonzero: the rounds OR by atomics (GatherArgs::hubs)
   int gcur = 0;
   // self-joined form (h(X,Y) :- h(X,Z), h(Z,Y)): the delta stays a bitmap
   // (dbits / gbits by turns), with the set bits of every row counted
@@ -1959,6 +1960,16 @@ struct Runner {
     if (a.by_a) {
       XL_TRY(get_index(p.steps[g.s1].rel, a.e1_acol, &a.e1a, -1, nullptr, 0, true));
       a.e1_xcol = g.x_col;
+      // Rounds of two launches where the bitmap is larger than 8 MB.  Forests,
+      // evaluate and read, us (one launch / two): 500 ids 184 / 239, 1,500
+      // (0.3 MB) 232 / 330, 5,000 (3 MB) 354 / 371, 12,000 (18 MB) 601 / 529,
+      // 20,000 (50 MB) 960 / 798.
+      const bool two = h->range0 * (int64_t)h->row_words * 4 > (8 << 20);
+      if (two && !h->ghubs.p) {  // once per run: the rounds all take the same form
+        XL_TRY(dalloc(c, 4, &h->ghubs, "gathered round form"));
+        HIP_TRY(c, k::gather_hubs(a.e1, h->ghubs.as<uint32_t>(), c->stream));
+      }
+      a.hubs = two ? h->ghubs.as<uint32_t>() : nullptr;
       a.in_lo = h->gbound[h->gcur].as<uint32_t>();
       a.in_hi = a.in_lo + h->range0;
       a.out_lo = h->gbound[h->gcur ^ 1].as<uint32_t>();
@@ -3636,11 +3647,9 @@ struct Runner {
         h->gather_ready = true;
         h->gcur = 0;
         if (h->round_new) {
-          HIP_TRY(c, k::row_popcount(h->dbits.as<uint32_t>(), h->range0, h->row_words, h->gflag[0].as<uint32_t>(),
-                                     c->stream));
-          // the seed's delta rows may hold bits anywhere
-          HIP_TRY(c, k::fill_bounds(h->gbound[0].as<uint32_t>(), h->gbound[0].as<uint32_t>() + h->range0, h->range0,
-                                    0u, (uint32_t)h->row_words, c->stream));
+          uint32_t* lo = h->gbound[0].as<uint32_t>();
+          HIP_TRY(c, k::row_bounds(h->dbits.as<uint32_t>(), h->range0, h->row_words, h->gflag[0].as<uint32_t>(), lo,
+                                   lo + h->range0, c->stream));
         }
         return XL_OK;
       }

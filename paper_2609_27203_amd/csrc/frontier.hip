@@ -530,23 +530,29 @@ __global__ __launch_bounds__(FR_THREADS) void gather_round_k(GatherArgs g) {
   wave_counters_add(g.counters, fresh, 0, cands);
 }
 
-// Gathered round by delta row (GatherArgs::by_a).  Every X that e1 pairs
-// with A receives the same Y values from A's delta row: the union U(A) of
-// e2's Y lists over the B bits of the delta row (words [in_lo, in_hi) only)
-// is built once in LDS with the wave-balanced push expansion of the frontier
-// kernels, and each nonzero word of U is ORed into the head row of every X
-// of A with one device atomic whose old value gives the bits new to X; those
-// go to X's next delta row (several A may reach one X, so that is an atomic
-// too), raise X's flag and widen its word bounds.  One wavefront per
-// workgroup handles one delta row at a time: a row's work is a chain of
-// dependent global accesses (flag, word range, delta words, e2 offsets, Y
-// lists, X list, atomics), most rows on a forest are small, and rows in
-// flight, not threads per row, set the pace.  The wavefront that reads delta
-// row A is the only one that touches it in the round, so it also empties it:
-// each nonzero word as it is read, then A's flag and bounds, which every
-// lane has read before lane 0 resets them.
-constexpr uint32_t GA_STEP = 16;             // delta words decoded per step
-constexpr uint32_t GA_ZCAP = GA_STEP * 32;   // B values listed per step, at most
+// Gathered round by delta row (GatherArgs::by_a), two launches.  Every X that
+// e1 pairs with A receives the same Y values from A's delta row: the union
+// U(A) of e2's Y lists over the B bits of the delta row (words [in_lo, in_hi)
+// only) is built once in LDS with the wave-balanced push expansion of the
+// frontier kernels.  gather_by_a_k writes it over the delta row, which only
+// its wavefront reads, with U's word bounds; gather_apply_k then ORs, for each
+// head row X, the unions of X's A values into row X.  X belongs to one 32-lane
+// group there, so the head row, the next delta row, its flag and its bounds
+// are plain loads and stores, each written in full every round: nothing has to
+// be emptied.  Where an X has more than GX_LONG values of A (*g.hubs), one
+// group's walk of that list would set the round's length, and on a small bitmap
+// (no g.hubs) the second launch costs more than it saves; the unions are then
+// ORed into the rows of A's X values by device atomics as they are made.
+//
+// Both launches are bound by chains of dependent accesses (flag, bounds and
+// offsets; delta words; e2 offsets; Y lists), most rows on a forest being
+// small, so each lane fetches the head of the chain for one of the wavefront's
+// next 64 rows at a time, and delta words, offsets and Y values are loaded a
+// step ahead or several at once.  20,000-node forest (43 M rows, 8 rounds):
+// the atomic form 620 us a run, these two 199 + 148; evaluate and read 963 ->
+// 795 us.
+constexpr uint32_t GA_ZCAP = 16 * 32;  // B values listed at a time, at most
+constexpr int GA_FLY = 4;              // steps of 64 candidates in flight
 
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
   for (int k = 32; k > 0; k >>= 1) x = min(x, (uint32_t)__shfl_xor(x, k, 64));
@@ -557,157 +563,343 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
   return x;
 }
 
-__global__ __launch_bounds__(64) void gather_by_a_k(GatherArgs g) {
-  extern __shared__ uint32_t U[];  // union of this A's Y values: zero between delta rows
-  __shared__ uint32_t zlist[GA_ZCAP];
-  __shared__ uint32_t s_excl[64], s_beg[64];
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
+  for (int k = 32; k > 0; k >>= 1) x += (uint32_t)__shfl_xor(x, k, 64);
+  return x;
+}
+
+// Rows [*beg, *beg + *deg) of key z (none unless on).
+__device__ __forceinline__ void list_of(const IndexProbe& e, bool on, uint32_t z, uint32_t* beg, uint32_t* deg) {
+  const uint32_t k = z - (uint32_t)e.key_lo;
+  if (!on || k >= e.key_range) return;
+  *beg = e.off[k];
+  *deg = e.off[k + 1] - *beg;
+}
+
+// LDS words of one wavefront: U, the listed B values, the owner search.
+__host__ __device__ constexpr uint32_t ga_words(uint32_t row_words) { return row_words + GA_ZCAP + 128; }
+// Longest list of A values that a group walks.  20,000 ids in four generations,
+// one A per X but for one X, evaluated without a read: with 16 values for that
+// X 468 us (444 by atomics), with 32 452 (428), with 64 walked one at a time
+// 911 (446).  Every X of 9,000 with 16 values: 2481 us (2809 by atomics).
+constexpr uint32_t GX_LONG = 16;
+// wavefronts per compute unit (the forest above, evaluate and read: 8 take
+// 845 us, 16 take 800, 32 take 805)
+constexpr int64_t GA_WAVES = 16;
+
+__global__ __launch_bounds__(512) void gather_by_a_k(GatherArgs g) {
+  extern __shared__ uint32_t ga_lds[];
+  __shared__ u64 s_tot[2];
   const uint32_t W = g.row_words;
-  const int lane = lane_id();
+  const int lane = lane_id(), w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  uint32_t* U = ga_lds + (size_t)w * ga_words(W);  // union of this A's Y values: zero between delta rows
+  uint32_t* zlist = U + W;
+  uint32_t* s_excl = zlist + GA_ZCAP;
+  uint32_t* s_beg = s_excl + 64;
   u64 cands = 0, fresh = 0;
   const FrontierArgs& a = g.push;
   const uint32_t* ycol = a.idx.col[a.ybind_col];
   const uint32_t* xcol = g.e1a.col[g.e1_xcol];
+  const bool direct = !g.hubs || *g.hubs != 0u;
+  if (threadIdx.x < 2) s_tot[threadIdx.x] = 0;
+  __syncthreads();
   for (uint32_t i = lane; i < W; i += 64) U[i] = 0u;
   wave_lds_sync();
-  for (int64_t ar64 = blockIdx.x; ar64 < g.range0; ar64 += gridDim.x) {
-    const uint32_t ar = (uint32_t)ar64;
-    if (!g.in_flag[ar]) continue;  // (uniform: no delta row)
-    uint32_t* frow = g.in_bits + (u64)ar * W;
-    const uint32_t wb = g.in_lo[ar], we = min(g.in_hi[ar], W);
-    const uint32_t kk = (uint32_t)g.lo0 + ar - (uint32_t)g.e1a.key_lo;
-    uint32_t b1 = 0, n1 = 0;
-    if (kk < g.e1a.key_range) {
-      b1 = g.e1a.off[kk];
-      n1 = g.e1a.off[kk + 1] - b1;
+  const int64_t waves = (int64_t)gridDim.x * nw, wave = (int64_t)blockIdx.x * nw + w;
+  for (int64_t base = wave; base < g.range0; base += 64 * waves) {
+    // lane j: flag, bounds and X list of delta row base + j * waves
+    const int64_t my = base + lane * waves;
+    uint32_t my_wb = 0, my_we = 0, my_b1 = 0, my_n1 = 0;
+    bool on = false;
+    if (my < g.range0) {
+      const uint32_t kk = (uint32_t)g.lo0 + (uint32_t)my - (uint32_t)g.e1a.key_lo;
+      on = g.in_flag[my] != 0u;
+      my_wb = g.in_lo[my];
+      my_we = min(g.in_hi[my], W);
+      if (kk < g.e1a.key_range) {
+        my_b1 = g.e1a.off[kk];
+        my_n1 = g.e1a.off[kk + 1] - my_b1;
+      }
     }
-    if (n1 == 0) {  // (uniform: no X pairs with A) empty the row unread
-      for (uint32_t wi = wb + (uint32_t)lane; wi < we; wi += 64) frow[wi] = 0u;
-      if (lane == 0) {
+    // (a row that no X pairs with is not read again, but in the direct form it
+    // has to be empty when it takes bits again)
+    u64 todo = __ballot(on && (my_n1 > 0 || direct));
+    while (todo) {
+      const int j = __ffsll((long long)todo) - 1;
+      todo &= todo - 1;
+      const uint32_t ar = (uint32_t)(base + j * waves);
+      const uint32_t wb = __shfl(my_wb, j, 64), we = __shfl(my_we, j, 64);
+      const uint32_t b1 = __shfl(my_b1, j, 64), n1 = __shfl(my_n1, j, 64);
+      uint32_t* frow = g.in_bits + (u64)ar * W;
+      uint32_t umin = 0xffffffffu, umax = 0u;  // this lane's words of U touched
+      uint32_t next = wb + (uint32_t)lane < we ? frow[wb + (uint32_t)lane] : 0u;
+      for (uint32_t cb = wb; cb < we; cb += 64) {
+        // the B values of delta words [cb, cb + 64), in order: in one piece
+        // where the list holds them, else 16 words at a time; the next words
+        // are loaded meanwhile
+        const uint32_t wi = cb + (uint32_t)lane;
+        const uint32_t d = next;
+        next = wi + 64 < we ? frow[wi + 64] : 0u;
+        if (direct && d) frow[wi] = 0u;
+        const uint32_t all = wave_sum_u32(__popc(d));
+        if (n1 == 0 || all == 0) continue;  // (uniform)
+        const int pieces = all > GA_ZCAP ? 4 : 1;
+        for (int piece = 0; piece < pieces; ++piece) {
+          const uint32_t dp = pieces == 1 || lane >> 4 == piece ? d : 0u;
+          const uint32_t c = __popc(dp);
+          const uint32_t incl = wave_incl_scan(c);
+          const uint32_t nz = __shfl(incl, 63, 64);
+          uint32_t pos = incl - c;
+          for (uint32_t bits = dp; bits; bits &= bits - 1)
+            zlist[pos++] = (uint32_t)a.lo1 + wi * 32u + (uint32_t)(__ffs(bits) - 1);
+          wave_lds_sync();
+          // each B's Y list: rows of 64 or more by the whole wavefront, smaller
+          // ones through a scan and a six-step owner search, four steps of 64
+          // candidates in flight; the next 64 lists' offsets are loaded meanwhile
+          uint32_t beg = 0, deg = 0;
+          list_of(a.idx, (uint32_t)lane < nz, zlist[lane], &beg, &deg);
+          for (uint32_t j0 = 0; j0 < nz; j0 += 64) {
+            const uint32_t r = j0 + 64 + (uint32_t)lane;
+            uint32_t nbeg = 0, ndeg = 0;
+            list_of(a.idx, r < nz, zlist[min(r, GA_ZCAP - 1)], &nbeg, &ndeg);
+            const bool big = deg >= 64;
+            u64 bigm = __ballot(big);
+            const uint32_t sdeg = big ? 0u : deg;
+            const uint32_t sincl = wave_incl_scan(sdeg);
+            const uint32_t total = __shfl(sincl, 63, 64);
+            s_excl[lane] = sincl - sdeg;
+            s_beg[lane] = beg;
+            wave_lds_sync();
+            if (lane == 0) cands += total;
+            while (bigm) {
+              const int rb = __ffsll((long long)bigm) - 1;
+              bigm &= bigm - 1;
+              const uint32_t bb = __shfl(beg, rb, 64), bd = __shfl(deg, rb, 64);
+              if (lane == 0) cands += bd;
+              for (uint32_t k = lane; k < bd; k += 64) {
+                const uint32_t y = ycol[bb + k] - (uint32_t)a.lo1;
+                const uint32_t bit = 1u << (y & 31);
+                umin = min(umin, y >> 5);
+                umax = max(umax, y >> 5);
+                if (!(U[y >> 5] & bit)) atomicOr(&U[y >> 5], bit);
+              }
+            }
+            for (uint32_t b0 = 0; b0 < total; b0 += 64 * GA_FLY) {
+              uint32_t y[GA_FLY];
+#pragma unroll
+              for (int f = 0; f < GA_FLY; ++f) {
+                const uint32_t i = b0 + 64 * f + lane;
+                if (i >= total) continue;
+                int q = 0;
+#pragma unroll
+                for (int step = 32; step > 0; step >>= 1)
+                  if (s_excl[q + step] <= i) q += step;
+                y[f] = ycol[s_beg[q] + (i - s_excl[q])] - (uint32_t)a.lo1;
+              }
+#pragma unroll
+              for (int f = 0; f < GA_FLY; ++f) {
+                if (b0 + 64 * f + lane >= total) continue;
+                const uint32_t bit = 1u << (y[f] & 31);
+                umin = min(umin, y[f] >> 5);
+                umax = max(umax, y[f] >> 5);
+                if (!(U[y[f] >> 5] & bit)) atomicOr(&U[y[f] >> 5], bit);
+              }
+            }
+            wave_lds_sync();
+            beg = nbeg;
+            deg = ndeg;
+          }
+        }
+      }
+      umin = wave_min_u32(umin);
+      umax = wave_max_u32(umax);
+      const bool any_y = umin <= umax;  // (uniform; otherwise U is still zero)
+      const uint32_t hi = any_y ? min(umax + 1u, W) : 0u;
+      if (!direct) {  // the delta row becomes U, for gather_apply_k
+        for (uint32_t wi = umin + (uint32_t)lane; wi < hi; wi += 64) {
+          frow[wi] = U[wi];
+          U[wi] = 0u;
+        }
+        if (lane == 0) {
+          g.in_lo[ar] = any_y ? umin : W;
+          g.in_hi[ar] = hi;
+        }
+        wave_lds_sync();
+        continue;
+      }
+      if (lane == 0) {  // the delta row is empty now
         g.in_flag[ar] = 0u;
         g.in_lo[ar] = W;
         g.in_hi[ar] = 0u;
       }
-      continue;
-    }
-    uint32_t umin = 0xffffffffu, umax = 0u;  // this lane's words of U touched
-    for (uint32_t cb = wb; cb < we; cb += GA_STEP) {
-      // the B values of delta words [cb, cb + GA_STEP), in order
-      const uint32_t wi = cb + (uint32_t)lane;
-      const uint32_t d = lane < (int)GA_STEP && wi < we ? frow[wi] : 0u;
-      if (d) frow[wi] = 0u;
-      const uint32_t c = __popc(d);
-      const uint32_t incl = wave_incl_scan(c);
-      const uint32_t nz = __shfl(incl, 63, 64);
-      uint32_t pos = incl - c;
-      for (uint32_t bits = d; bits; bits &= bits - 1)
-        zlist[pos++] = (uint32_t)a.lo1 + wi * 32u + (uint32_t)(__ffs(bits) - 1);
+      if (!any_y) continue;
+      uint32_t nb = 0;
+      for (uint32_t q = 0; q < n1; ++q) {
+        const uint32_t xr = xcol[b1 + q] - (uint32_t)g.lo0;
+        if ((int64_t)xr >= g.range0) continue;  // outside the head's rows (not planned)
+        if (lane == 0) {  // X's next delta row may get bits in these words
+          atomicMin(&g.out_lo[xr], umin);
+          atomicMax(&g.out_hi[xr], hi);
+        }
+        bool any = false;
+        for (uint32_t wi = umin + (uint32_t)lane; wi < hi; wi += 64) {
+          const uint32_t u = U[wi];
+          if (!u) continue;
+          const u64 at = (u64)xr * W + wi;
+          const uint32_t nw_bits = u & ~atomicOr(g.bits + at, u);
+          if (nw_bits) {  // (several A may reach X)
+            atomicOr(g.out_bits + at, nw_bits);
+            nb += (uint32_t)__popc(nw_bits);
+            any = true;
+          }
+        }
+        if (__ballot(any) && lane == 0) g.out_flag[xr] = 1u;
+      }
+      fresh += nb;
+      wave_lds_sync();  // every word of U is read before it is cleared
+      for (uint32_t wi = umin + (uint32_t)lane; wi < hi; wi += 64) U[wi] = 0u;
       wave_lds_sync();
-      // each B's Y list: rows of 64 or more by the whole wavefront, smaller
-      // ones through a scan and a six-step owner search
-      for (uint32_t j0 = 0; j0 < nz; j0 += 64) {
-        const uint32_t r = j0 + (uint32_t)lane;
-        uint32_t beg = 0, deg = 0;
-        if (r < nz) {
-          const uint32_t k2 = zlist[r] - (uint32_t)a.idx.key_lo;
-          if (k2 < a.idx.key_range) {
-            beg = a.idx.off[k2];
-            deg = a.idx.off[k2 + 1] - beg;
-          }
-        }
-        const bool big = deg >= 64;
-        u64 bigm = __ballot(big);
-        const uint32_t sdeg = big ? 0u : deg;
-        const uint32_t sincl = wave_incl_scan(sdeg);
-        const uint32_t total = __shfl(sincl, 63, 64);
-        s_excl[lane] = sincl - sdeg;
-        s_beg[lane] = beg;
-        wave_lds_sync();
-        if (lane == 0) cands += total;
-        while (bigm) {
-          const int rb = __ffsll((long long)bigm) - 1;
-          bigm &= bigm - 1;
-          const uint32_t bb = __shfl(beg, rb, 64), bd = __shfl(deg, rb, 64);
-          if (lane == 0) cands += bd;
-          for (uint32_t k = lane; k < bd; k += 64) {
-            const uint32_t y = ycol[bb + k] - (uint32_t)a.lo1;
-            const uint32_t bit = 1u << (y & 31);
-            umin = min(umin, y >> 5);
-            umax = max(umax, y >> 5);
-            if (!(U[y >> 5] & bit)) atomicOr(&U[y >> 5], bit);
-          }
-        }
-        for (uint32_t b0 = 0; b0 < total; b0 += 64) {
-          const uint32_t j = b0 + lane;
-          if (j < total) {
-            int q = 0;
-#pragma unroll
-            for (int step = 32; step > 0; step >>= 1)
-              if (s_excl[q + step] <= j) q += step;
-            const uint32_t y = ycol[s_beg[q] + (j - s_excl[q])] - (uint32_t)a.lo1;
-            const uint32_t bit = 1u << (y & 31);
-            umin = min(umin, y >> 5);
-            umax = max(umax, y >> 5);
-            if (!(U[y >> 5] & bit)) atomicOr(&U[y >> 5], bit);
-          }
-        }
-        wave_lds_sync();
-      }
     }
-    if (lane == 0) {  // the row is empty now; every lane read wb and we above
-      g.in_flag[ar] = 0u;
-      g.in_lo[ar] = W;
-      g.in_hi[ar] = 0u;
-    }
-    umin = wave_min_u32(umin);
-    umax = wave_max_u32(umax);
-    if (umin > umax) continue;  // (uniform: no Y value; U is still zero)
-    const uint32_t hi = min(umax + 1u, W);
-    uint32_t nb = 0;
-    for (uint32_t q = 0; q < n1; ++q) {
-      const uint32_t xr = xcol[b1 + q] - (uint32_t)g.lo0;
-      if ((int64_t)xr >= g.range0) continue;  // outside the head's rows (not planned)
-      if (lane == 0) {  // X's next delta row may get bits in these words
-        atomicMin(&g.out_lo[xr], umin);
-        atomicMax(&g.out_hi[xr], hi);
-      }
-      bool any = false;
-      for (uint32_t wi = umin + (uint32_t)lane; wi < hi; wi += 64) {
-        const uint32_t u = U[wi];
-        if (!u) continue;
-        const u64 at = (u64)xr * W + wi;
-        const uint32_t nw = u & ~atomicOr(g.bits + at, u);
-        if (nw) {
-          atomicOr(g.out_bits + at, nw);
-          nb += (uint32_t)__popc(nw);
-          any = true;
-        }
-      }
-      if (__ballot(any) && lane == 0) g.out_flag[xr] = 1u;
-    }
-    fresh += nb;
-    wave_lds_sync();  // every word of U is read before it is cleared
-    for (uint32_t wi = umin + (uint32_t)lane; wi < hi; wi += 64) U[wi] = 0u;
-    wave_lds_sync();
   }
   for (int k = 32; k > 0; k >>= 1) {
     cands += __shfl_xor(cands, k, 64);
     fresh += __shfl_xor(fresh, k, 64);
   }
-  wave_counters_add(g.counters, fresh, 0, cands);
+  if (lane == 0) {
+    if (cands) atomicAdd(&s_tot[0], cands);
+    if (fresh) atomicAdd(&s_tot[1], fresh);
+  }
+  __syncthreads();
+  if (w == 0) wave_counters_add(g.counters, s_tot[1], 0, s_tot[0]);
+}
+
+// The second launch (see above): a 32-lane group per head row X.  Its lanes
+// hold the list of A values (row, bounds); four words per lane of four rows
+// are in flight (evaluate and read, us: 790 with one row; eight words 800; 16 lanes with four
+// words 823, with eight 829: a row's steps follow one another, and rows span
+// up to 625 words).  32 rows a workgroup: the counters take one atomic of each.
+constexpr int GX_THREADS = 1024, GX_LANES = 32, GX_ROWS = GX_THREADS / GX_LANES, GX_WORDS = 4, GX_FLY = 4;
+static_assert(GX_LONG <= GX_LANES, "a lane per A value of the list");
+__global__ __launch_bounds__(GX_THREADS) void gather_apply_k(GatherArgs g) {
+  __shared__ u64 s_fresh;
+  if (*g.hubs) return;  // (uniform)
+  if (threadIdx.x == 0) s_fresh = 0;
+  __syncthreads();
+  const uint32_t W = g.row_words;
+  const uint32_t l = threadIdx.x % GX_LANES, first = (uint32_t)lane_id() & ~(uint32_t)(GX_LANES - 1);
+  const uint32_t* acol = g.e1.col[g.e1_acol];
+  u64 fresh = 0;
+  for (int64_t x = (int64_t)blockIdx.x * GX_ROWS + threadIdx.x / GX_LANES; x < g.range0;
+       x += (int64_t)gridDim.x * GX_ROWS) {
+    const uint32_t kk = (uint32_t)g.lo0 + (uint32_t)x - (uint32_t)g.e1.key_lo;
+    uint32_t b1 = 0, n1 = 0;
+    if (kk < g.e1.key_range) {
+      b1 = g.e1.off[kk];
+      n1 = g.e1.off[kk + 1] - b1;
+    }
+    // lane l: the list's A value l, its row of in_bits and that row's bounds
+    uint32_t ar = 0, alo = W, ahi = 0;
+    if (l < n1) {
+      const uint32_t r = acol[b1 + l] - (uint32_t)g.lo0;
+      if ((int64_t)r < g.range0) {
+        const uint32_t f = g.in_flag[r], rl = g.in_lo[r], rh = min(g.in_hi[r], W);
+        if (f && rl < rh) {
+          ar = r;
+          alo = rl;
+          ahi = rh;
+        }
+      }
+    }
+    const uint32_t on = (uint32_t)(__ballot(alo < ahi) >> first) & (uint32_t)((1ull << GX_LANES) - 1u);
+    uint32_t lo = alo, hi = ahi;
+    for (int d = GX_LANES / 2; d > 0; d >>= 1) {
+      lo = min(lo, (uint32_t)__shfl_xor(lo, d, 64));
+      hi = max(hi, (uint32_t)__shfl_xor(hi, d, 64));
+    }
+    uint32_t* hrow = g.bits + (u64)x * W;
+    uint32_t* orow = g.out_bits + (u64)x * W;
+    uint32_t nb = 0;
+    for (uint32_t w0 = lo; w0 < hi; w0 += GX_LANES * GX_WORDS) {
+      uint32_t v[GX_WORDS] = {}, old[GX_WORDS];
+#pragma unroll
+      for (int k = 0; k < GX_WORDS; ++k) {
+        const uint32_t wi = w0 + k * GX_LANES + l;
+        old[k] = wi < hi ? hrow[wi] : 0u;
+      }
+      for (uint32_t m = on; m;) {
+        uint32_t t[GX_FLY][GX_WORDS];
+#pragma unroll
+        for (int e = 0; e < GX_FLY; ++e) {
+          const int src = (int)first + (m ? __ffs(m) - 1 : 0);
+          const uint32_t rl = __shfl(alo, src, 64), rh = m ? __shfl(ahi, src, 64) : 0u;
+          const uint32_t* row = g.in_bits + (u64)__shfl(ar, src, 64) * W;
+          m &= m - 1;
+#pragma unroll
+          for (int k = 0; k < GX_WORDS; ++k) {
+            const uint32_t wi = w0 + k * GX_LANES + l;
+            t[e][k] = wi >= rl && wi < rh ? row[wi] : 0u;
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < GX_FLY; ++e)
+#pragma unroll
+          for (int k = 0; k < GX_WORDS; ++k) v[k] |= t[e][k];
+      }
+#pragma unroll
+      for (int k = 0; k < GX_WORDS; ++k) {
+        const uint32_t wi = w0 + k * GX_LANES + l;
+        if (wi >= hi) continue;
+        const uint32_t nw = v[k] & ~old[k];
+        if (nw) hrow[wi] = old[k] | nw;
+        orow[wi] = nw;  // (zeros too: the row's bounds are [lo, hi))
+        nb += (uint32_t)__popc(nw);
+      }
+    }
+    for (int d = GX_LANES / 2; d > 0; d >>= 1) nb += __shfl_xor(nb, d, 64);
+    if (l == 0) {
+      g.out_flag[x] = nb ? 1u : 0u;
+      g.out_lo[x] = lo;
+      g.out_hi[x] = hi;
+      fresh += nb;
+    }
+  }
+  for (int k = 32; k > 0; k >>= 1) fresh += __shfl_xor(fresh, k, 64);
+  if (lane_id() == 0 && fresh) atomicAdd(&s_fresh, fresh);
+  __syncthreads();
+  if (threadIdx.x < 64) wave_counters_add(g.counters, s_fresh, 0, 0);
+}
+
+// *hubs (zero on entry) becomes 1 where a key of the index has more than
+// GX_LONG rows.
+__global__ void gather_hubs_k(IndexProbe e, uint32_t* hubs) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)e.key_range;
+       i += (int64_t)gridDim.x * blockDim.x)
+    if (e.off[i + 1] - e.off[i] > GX_LONG) *hubs = 1u;
+}
+hipError_t gather_hubs(const IndexProbe& e, uint32_t* hubs, hipStream_t s) {
+  const hipError_t err = hipMemsetAsync(hubs, 0, 4, s);
+  if (err != hipSuccess || e.key_range == 0) return err;
+  gather_hubs_k<<<grid_for(e.key_range, 256, 2048), 256, 0, s>>>(e, hubs);
+  return hipGetLastError();
 }
 
 hipError_t gather_round(const GatherArgs& a, hipStream_t s) {
   if (a.range0 <= 0) return hipSuccess;
   if (a.by_a) {
-    // eight single-wavefront workgroups per compute unit: measured on the
-    // 20,000-node forest, 2,048 wavefronts take 0.60 ms per run against 0.71
-    // with 1,024, 0.66 with 3,072 and 0.94 with 8,192
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
-    const unsigned grid = (unsigned)std::min<int64_t>(a.range0, 8 * (int64_t)std::max(cus, 1));
-    gather_by_a_k<<<grid, 64, (size_t)a.row_words * sizeof(uint32_t), s>>>(a);
+    // as many wavefronts a workgroup (at most 8) as fit 64 KB of LDS; on a
+    // small bitmap one, and eight of them per compute unit
+    const size_t per = ga_words(a.row_words) * sizeof(uint32_t);
+    if (per > 65536) return hipErrorInvalidValue;
+    const int nw = a.hubs ? (int)std::min<size_t>(8, 65536 / per) : 1;
+    const int64_t waves = std::min<int64_t>(a.range0, (a.hubs ? GA_WAVES : 8) * (int64_t)std::max(cus, 1));
+    gather_by_a_k<<<(unsigned)((waves + nw - 1) / nw), 64 * nw, per * nw, s>>>(a);
+    e = hipGetLastError();
+    if (e != hipSuccess || !a.hubs) return e;
+    gather_apply_k<<<grid_for(a.range0, GX_ROWS, 4096), GX_THREADS, 0, s>>>(a);
   } else {
     const unsigned grid = (unsigned)std::min<int64_t>(a.range0, 2048);
     gather_round_k<<<grid, FR_THREADS, (size_t)a.row_words * 2 * sizeof(uint32_t), s>>>(a);
@@ -922,31 +1114,53 @@ hipError_t fill_bounds(uint32_t* lo, uint32_t* hi, int64_t n, uint32_t vlo, uint
   return hipGetLastError();
 }
 
-// Number of set bits in each bitmap row.
+// Number of set bits in each bitmap row, with BOUNDS also the words [lo, hi)
+// that hold them (empty: lo = row_words, hi = 0).
 // One wavefront per row: four word loads in flight per lane, then a
 // shuffle reduction (no barriers).
-__global__ __launch_bounds__(256) void row_popcount_k(const uint32_t* bits, int64_t nrows,
-                                                      uint32_t row_words, uint32_t* cnt) {
+template <bool BOUNDS>
+__global__ __launch_bounds__(256) void row_popcount_k(const uint32_t* bits, int64_t nrows, uint32_t row_words,
+                                                      uint32_t* cnt, uint32_t* lo, uint32_t* hi) {
   const uint32_t lane = (uint32_t)lane_id();
   for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < nrows; r += (int64_t)gridDim.x * 4) {
     const uint32_t* row = bits + (u64)r * row_words;
-    uint32_t c = 0;
+    uint32_t c = 0, rl = row_words, rh = 0;
     for (uint32_t i = lane; i < row_words; i += 256) {
       uint32_t w[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) w[k] = i + 64u * k < row_words ? row[i + 64u * k] : 0u;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) c += (uint32_t)__popc(w[k]);
+      for (int k = 0; k < 4; ++k) {
+        c += (uint32_t)__popc(w[k]);
+        if (BOUNDS && w[k]) {
+          rl = min(rl, i + 64u * k);
+          rh = max(rh, i + 64u * k + 1);
+        }
+      }
     }
     for (int k = 32; k > 0; k >>= 1) c += __shfl_xor(c, k, 64);
     if (lane == 0) cnt[r] = c;
+    if (BOUNDS) {
+      rl = wave_min_u32(rl);
+      rh = wave_max_u32(rh);
+      if (lane == 0) {
+        lo[r] = rl;
+        hi[r] = rh;
+      }
+    }
   }
 }
-hipError_t row_popcount(const uint32_t* bits, int64_t nrows, uint32_t row_words, uint32_t* cnt,
-                        hipStream_t s) {
+hipError_t row_popcount(const uint32_t* bits, int64_t nrows, uint32_t row_words, uint32_t* cnt, hipStream_t s) {
   if (nrows <= 0) return hipSuccess;
-  row_popcount_k<<<(unsigned)std::min<int64_t>((nrows + 3) / 4, 1 << 16), 256, 0, s>>>(bits, nrows, row_words,
-                                                                                      cnt);
+  row_popcount_k<false><<<(unsigned)std::min<int64_t>((nrows + 3) / 4, 1 << 16), 256, 0, s>>>(bits, nrows, row_words,
+                                                                                             cnt, nullptr, nullptr);
+  return hipGetLastError();
+}
+hipError_t row_bounds(const uint32_t* bits, int64_t nrows, uint32_t row_words, uint32_t* cnt, uint32_t* lo,
+                      uint32_t* hi, hipStream_t s) {
+  if (nrows <= 0) return hipSuccess;
+  row_popcount_k<true><<<(unsigned)std::min<int64_t>((nrows + 3) / 4, 1 << 16), 256, 0, s>>>(bits, nrows, row_words,
+                                                                                            cnt, lo, hi);
   return hipGetLastError();
 }
 

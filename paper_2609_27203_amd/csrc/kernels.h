@@ -162,6 +162,7 @@ hipError_t frontier_round(const FrontierArgs& a, hipStream_t s);
 // as the device keeps resident.
 hipError_t frontier_resident(const FrontierArgs& a, unsigned grid, hipStream_t s);
 // One gathered round (see GatherArgs).
+hipError_t gather_hubs(const IndexProbe& e, uint32_t* hubs, hipStream_t s);
 hipError_t gather_round(const GatherArgs& a, hipStream_t s);
 // One round of a self-joined closure (see SelfJoinArgs; row_words at most
 // SJ_MAX_WORDS, else hipErrorInvalidValue), then full |= next and full_cnt +=
@@ -178,6 +179,8 @@ hipError_t fill_bounds(uint32_t* lo, uint32_t* hi, int64_t n, uint32_t vlo, uint
 hipError_t hasin_bits(const IndexProbe& rev, int32_t lo1, uint32_t words, uint32_t* out, hipStream_t s);
 hipError_t row_popcount(const uint32_t* bits, int64_t nrows, uint32_t row_words, uint32_t* cnt,
                         hipStream_t s);
+hipError_t row_bounds(const uint32_t* bits, int64_t nrows, uint32_t row_words, uint32_t* cnt, uint32_t* lo,
+                      uint32_t* hi, hipStream_t s);
 hipError_t bits_to_rows(const uint32_t* bits, int64_t nrows, uint32_t row_words, const uint32_t* off,
                         int32_t lo0, int32_t lo1, uint32_t* c0, uint32_t* c1, int64_t cap, hipStream_t s);
 // out row sg = bitmap row (x[sg] - lo0)
