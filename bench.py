@@ -38,6 +38,7 @@ import hashlib
 import json
 import os
 import platform
+import re
 import statistics
 import sys
 import time
@@ -65,22 +66,22 @@ DESCRIPTIONS = {
 # dominant kernel family of each workload and the kernel the counters cover
 FAMILY = {"tc_uniform": "front", "tc_rmat_count": "front", "sssp": "emit", "lse_dag": "pull",
           "same_generation": "gather", "triangle": "wcoj"}
-KERNEL = {
+KERNEL = {  # regular expressions of the kernels' names
     "front": "frontier_resident_k",
-    "emit": "dense_min_tile_k",
-    "pull": "dense_pull_k",
-    "gather": "gather_by_a_k",
+    "emit": "dense_min_fast_k",
+    "pull": "dense_pull_marks_k",
+    "gather": "gather_(by_a|apply)_k",
     "wcoj": "wcoj_probe_k",
 }
 KERNEL_DOC = {
     "front": "frontier_resident_k (every round of a first key in one workgroup, its row in LDS: delta "
              "expand or in-edge pull + membership test + merge)",
-    "emit": "dense_min_tile_k (one workgroup per source and tile of targets, the tile's values in LDS: "
+    "emit": "dense_min_fast_k (one workgroup per source and tile of targets, the tile's values in LDS: "
             "delta rows expanded through the (tile, Z) index, min folded in LDS)",
-    "pull": "dense_pull_k (fold of each marked key's in-edges against the delta, keys ordered by target)",
-    "gather": "gather_by_a_k (one workgroup per delta row A: the union of e2's Y lists over A's B bits "
-              "built once in LDS, its nonzero words ORed into the head rows of A's X values with device "
-              "atomics whose old values give the next delta words)",
+    "pull": "dense_pull_marks_k (fold of each marked key's in-edges against the delta, keys ordered by target, "
+            "read from the mark words)",
+    "gather": "gather_by_a_k + gather_apply_k (one wavefront per delta row A: the union of e2's Y lists over "
+              "A's B bits built once in LDS; then 32 lanes per head row X OR the unions of X's A values into it)",
     "wcoj": "wcoj_probe_k (count and materialize passes: each driver row's shorter Z list probed into "
             "the longer)",
 }
@@ -403,7 +404,7 @@ def _counter_rows(d, kernel=None):
     rows = []
     for f in glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True):
         for r in csv.DictReader(open(f)):
-            if kernel is None or kernel in r["Kernel_Name"]:
+            if kernel is None or re.search(kernel, r["Kernel_Name"]):
                 rows.append(r)
     return rows
 
@@ -432,10 +433,10 @@ def profile_commands(d, name):
     cmds = [f"rocprofv3 --kernel-trace --stats -d {d}/{name}/trace -o run --output-format csv -- "
             f"python3 bench.py --workload {name} {TRACE_ARGS}"]
     for ctr in ("FETCH_SIZE", "WRITE_SIZE"):
-        cmds.append(f"rocprofv3 --pmc {ctr} --kernel-include-regex {kern} -d {d}/{name}/{ctr} -o run "
+        cmds.append(f"rocprofv3 --pmc {ctr} --kernel-include-regex '{kern}' -d {d}/{name}/{ctr} -o run "
                     f"--output-format csv -- python3 bench.py --workload {name} {PMC_ARGS}")
     for i, grp in enumerate(SQ_PASSES):
-        cmds.append(f"rocprofv3 --pmc {grp} --kernel-include-regex {kern} -d {d}/{name}/sq/p{i + 1} -o run "
+        cmds.append(f"rocprofv3 --pmc {grp} --kernel-include-regex '{kern}' -d {d}/{name}/sq/p{i + 1} -o run "
                     f"--output-format csv -- python3 bench.py --workload {name} {PMC_ARGS}")
     return cmds
 
