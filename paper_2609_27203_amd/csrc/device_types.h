@@ -39,14 +39,15 @@ struct MicroOp {
 // of q's rows projected onto the literal's constrained columns (variables and
 // constants; none, one, or two int32 columns packed (v0 << 32) | v1 as
 // unsigned), searched per candidate; or, for one column over a range not much
-// wider than its rows, a bitmap of its values (bit v - lo, v - lo < range).
+// wider than its rows, a bitmap of its values (bit v - lo, v - lo <= last: the
+// whole int32 range has 2^32 of them).
 // With no constrained column the literal only asks whether q has a row (n > 0).
 constexpr int MAXNEG = 2;
 struct NegTable {
   const unsigned long long* keys;
   int64_t n;
   const uint32_t* bits;
-  uint32_t lo, range;
+  uint32_t lo, last;
 };
 
 // Rows that drive a stage: a relation, a delta, or materialized bindings

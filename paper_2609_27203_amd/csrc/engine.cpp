@@ -852,9 +852,9 @@ struct DevNeg {
   int col[2] = {0, 0};
   Buf keys, bits;
   int64_t n = 0;
-  uint32_t lo = 0, range = 0;
+  uint32_t lo = 0, last = 0;
   NegTable table() const {
-    return NegTable{keys.as<unsigned long long>(), n, bits.as<uint32_t>(), lo, range};
+    return NegTable{keys.as<unsigned long long>(), n, bits.as<uint32_t>(), lo, last};
   }
 };
 
@@ -1857,7 +1857,7 @@ struct Runner {
       kp.lo[0] = q->lo[np.col[0]];
       HIP_TRY(c, k::bits_set_rows(t->bits.as<uint32_t>(), 1, q->col[np.col[0]], nullptr, t->n, kp, c->stream));
       t->lo = (uint32_t)kp.lo[0];
-      t->range = (uint32_t)range;
+      t->last = (uint32_t)(range - 1);
     } else if (np.ncols > 0 && t->n > 0) {
       // (rows in canonical order without negative values project to ascending
       // unsigned keys on their leading columns)

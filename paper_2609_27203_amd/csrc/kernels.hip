@@ -1562,7 +1562,7 @@ __device__ __forceinline__ bool neg_member(const NegTable t, int ncols, uint32_t
   if (ncols == 0) return t.n > 0;
   if (t.bits) {
     const uint32_t b = x - t.lo;
-    return b < t.range && ((t.bits[b >> 5] >> (b & 31)) & 1u);
+    return b <= t.last && ((t.bits[b >> 5] >> (b & 31)) & 1u);
   }
   const u64 k = ncols == 1 ? (u64)x : ((u64)x << 32) | y;
   int64_t lo = 0, hi = t.n;
@@ -1585,7 +1585,7 @@ __device__ __forceinline__ bool run_ops(A& a, Regs& u) {
     if (op.kind == OP_CMP) {
       ok = ok && compare(op.cmp, op.type, x, operand(a, u, op.b));
     } else if (op.kind == OP_NOTIN) {
-      const NegTable t = {a.neg[op.cmp].keys, a.neg[op.cmp].n, a.neg[op.cmp].bits, a.neg[op.cmp].lo, a.neg[op.cmp].range};
+      const NegTable t = {a.neg[op.cmp].keys, a.neg[op.cmp].n, a.neg[op.cmp].bits, a.neg[op.cmp].lo, a.neg[op.cmp].last};
       ok = ok && !neg_member(t, op.type, x, op.type > 1 ? operand(a, u, op.b) : 0u);
     } else if (op.kind == OP_MOV) {
       setv(u, op.dst, x);

@@ -84,3 +84,28 @@ def test_negated_relations(span, lo):
     for name, rows in want.items():
         assert list(zip(*[c.tolist() for c in ctx.relations[name].read()])) == sorted(rows), name
     ctx.close()
+
+
+@pytest.mark.parametrize("low,high", [(-2**31, 2**31 - 1), (-2**31, 2**31 - 2), (-2**31 + 1, 2**31 - 1)])
+def test_negated_column_over_the_whole_range(low, high):
+    """2^25 rows whose bounds are (nearly) those of int32: a bitmap of up to 2^32 bits."""
+    import torch
+
+    from paper_2609_27203_amd import xlh
+    print(f"case: negation over [{low}, {high}]", flush=True)
+    n = 1 << 25
+    q = low + 128 * torch.arange(n, dtype=torch.int64, device="cuda")
+    q[-1] = high
+    rng = np.random.default_rng(7)
+    x = np.r_[-2**31, 2**31 - 1, high, low, low + 1, high - 1, low + 128 * rng.integers(0, n - 1, 500),
+              rng.integers(-2**31, 2**31, 500)].astype(np.int32)
+    ctx = xlh.Context(device=0, workspace_bytes=4 << 30)
+    ctx.relation("q", ("i32",)).load([q.to(torch.int32)])
+    ctx.relation("e", ("i32",)).load([x])
+    ctx.relation("keep", ("i32",))
+    ctx.compile("keep(X) :- e(X), not q(X).").run()
+    off = x.astype(np.int64) - low
+    in_q = (x == high) | ((off >= 0) & (off % 128 == 0) & (off // 128 < n - 1))
+    assert 0 < in_q.sum() < len(x)
+    assert np.array_equal(ctx.relations["keep"].read()[0], np.unique(x[~in_q]))
+    ctx.close()
