@@ -2483,7 +2483,11 @@ __device__ __forceinline__ void pull_fold8(int fast, int type, bool lse, const u
       x[q] = on[q] ? __uint_as_float(fast_value(fast, T_F32, cv[q], wv[q])) : -INFINITY;
       nm = fmaxf(nm, x[q]);
     }
-    if (nm == -INFINITY) return;
+    if (fabsf(nm) == INFINITY) {  // the value itself (x - nm would be NaN)
+      m = nm;
+      facc = 1.0f;
+      return;
+    }
     facc = m == nm ? facc : m == -INFINITY ? 0.0f : facc * expf(m - nm);
     m = nm;
 #pragma unroll
@@ -2531,22 +2535,6 @@ __device__ __forceinline__ uint32_t pull_fold(PullArgs& a, uint32_t t, bool act,
     float m = -INFINITY, facc = 0.0f;
     uint32_t uacc = 0;
     bool any = false;
-    auto fold = [&](uint32_t x) {
-      any = true;
-      if (lse) {
-        const float xv = __uint_as_float(x);
-        if (xv > m) {
-          facc = (m == -INFINITY ? 0.0f : facc * expf(m - xv)) + 1.0f;
-          m = xv;
-        } else if (xv != -INFINITY) {
-          facc += expf(xv - m);
-        }
-      } else if (f32) {
-        facc = __fadd_rn(facc, __uint_as_float(x));
-      } else {
-        uacc += x;
-      }
-    };
     if constexpr (FAST) {
       // the value is one add/subtract of the delta value and a column of
       // e: eight in-edges at a time, each level of loads issued together
