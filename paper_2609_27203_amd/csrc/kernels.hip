@@ -1628,7 +1628,8 @@ __device__ __forceinline__ bool eval_ops(KernArgs& a, Regs& u) {
 __device__ __forceinline__ double lse2d(double a, double b) {
   if (a == -HUGE_VAL) return b;
   if (b == -HUGE_VAL) return a;
-  return fmax(a, b) + log1p(exp(-fabs(a - b)));
+  const double m = fmax(a, b);
+  return m == HUGE_VAL ? m : m + log1p(exp(-fabs(a - b)));
 }
 __device__ __forceinline__ u64 acc_identity(int type, int fold_kind) {
   if (fold_kind == FOLD_LSE) return (u64)__double_as_longlong(-HUGE_VAL);
@@ -2339,7 +2340,7 @@ __device__ __forceinline__ float lse2(float a, float b) {
   if (a == -INFINITY) return b;
   if (b == -INFINITY) return a;
   const float m = fmaxf(a, b);
-  return m + log1pf(expf(-fabsf(a - b)));
+  return m == INFINITY ? m : m + log1pf(expf(-fabsf(a - b)));
 }
 
 // Delta rows of batched keyed-table rounds: list positions [bnd[j], bnd[j + 1])
@@ -2573,7 +2574,7 @@ __device__ __forceinline__ uint32_t pull_fold(PullArgs& a, uint32_t t, bool act,
         if (xv > m) {
           facc = (m == -INFINITY ? 0.0f : facc * expf(m - xv)) + 1.0f;
           m = xv;
-        } else if (xv != -INFINITY) {
+        } else if (xv != -INFINITY && m != INFINITY) {
           facc += expf(xv - m);
         }
       } else if (f32) {
@@ -2625,7 +2626,10 @@ __device__ __forceinline__ uint32_t pull_fold(PullArgs& a, uint32_t t, bool act,
       if (is_tail && oks > 0) {
         const float m = __uint_as_float(L.m[q]), acc = __uint_as_float(L.acc[q]);
         float nm = m, nacc = acc;
-        if (mrun != -INFINITY) {
+        if (mrun == INFINITY || m == INFINITY) {  // the value itself
+          nm = INFINITY;
+          nacc = 1.0f;
+        } else if (mrun != -INFINITY) {
           if (mrun > m) {
             nacc = (m == -INFINITY ? 0.0f : acc * expf(m - mrun)) + srun;
             nm = mrun;
@@ -3582,8 +3586,8 @@ __global__ void seg_reduce_k(const K* keys, const uint32_t* vals, const uint32_t
     } else if (fold_kind == FOLD_LSE) {
       float m = -INFINITY;
       for (uint32_t i = b; i < e; ++i) m = fmaxf(m, __uint_as_float(vals[i]));
-      if (m == -INFINITY) {
-        out = __float_as_uint(-INFINITY);
+      if (fabsf(m) == INFINITY) {
+        out = __float_as_uint(m);
       } else {
         float acc = 0.0f;
         for (uint32_t i = b; i < e; ++i) acc += expf(__uint_as_float(vals[i]) - m);
