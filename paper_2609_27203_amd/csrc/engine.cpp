@@ -4268,6 +4268,7 @@ struct Runner {
       st->new_tuples_total += d;
     }
     const int32_t seed_record = st->rounds_recorded;
+    const int64_t seeded = total;
     record(total);
     if (s.recursive && total > 0 && batched_tiles(s)) {
       XL_TRY(run_tiles_batched(s.variants[0], heads[0].get(), max_iterations));
@@ -4328,13 +4329,13 @@ struct Runner {
                     indexes.end());
     kept.clear();
     for (auto& h : heads) XL_TRY(materialize(h.get()));
-    if (!s.recursive && seed_record < XL_STATS_ROUNDS) {
-      // a non-recursive stratum records the rows it produced; aggregate heads
-      // built from sorted segments or index degrees only have them now
+    if (!s.recursive) {
+      // a non-recursive stratum records the rows it produced; heads built from
+      // sorted candidates, counters or index degrees only have them now
       int64_t produced = -rows_before;
       for (auto& h : heads) produced += h->rel->nrows;
-      st->new_tuples_total += produced - st->delta_rows[seed_record];
-      st->delta_rows[seed_record] = produced;
+      st->new_tuples_total += produced - seeded;
+      if (seed_record < XL_STATS_ROUNDS) st->delta_rows[seed_record] = produced;
     }
     for (auto& ix : kept) indexes.push_back(std::move(ix));
     kept.clear();

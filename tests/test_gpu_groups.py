@@ -161,3 +161,36 @@ def test_scanned_set_capacity_and_resume():
         with pytest.raises(xlh.XlError):  # 1,001 rows now
             prog.run()
         ctx.close()
+
+
+RECEIPT_RULES = """
+tc(X,Y) :- e(X,Y).
+tc(X,Y) :- tc(X,Z), e(Z,Y).
+far(X,max(Y)) :- tc(X,Y).
+near(X,min(Y)) :- tc(X,Y).
+n(X,count(Y)) :- tc(X,Y).
+total(X,sum(Y)) :- tc(X,Y).
+wide(X,Y) :- w(X,Y).
+"""
+
+
+@pytest.mark.parametrize("profile", [0, 1])
+@pytest.mark.parametrize("passes", [3, 255, 256, 300])
+def test_receipt_after_many_passes(passes, profile):
+    """Strata after the last recorded round still count in new_tuples_total."""
+    from paper_2609_27203_amd import xlh
+    print(f"case: receipt passes={passes} profile={profile}", flush=True)
+    x = np.arange(passes, dtype=np.int32)
+    ctx = xlh.Context(device=0, workspace_bytes=256 << 20)
+    ctx.set_option("profile", profile)
+    ctx.relation("e", ("i32", "i32")).load([x, x + 1])
+    ctx.relation("w", ("i32", "i32")).load([x * 7_000_003, x * 5_000_011])
+    for name, k in (("tc", 2), ("far", 2), ("near", 2), ("n", 2), ("total", 2), ("wide", 2)):
+        ctx.relation(name, ("i32",) * k)
+    st = ctx.compile(RECEIPT_RULES).run()
+    assert st["rounds_recorded"] >= passes + 5
+    assert st["derived_tuples"] == passes * (passes + 1) // 2 + 5 * passes
+    assert st["new_tuples_total"] == st["derived_tuples"]
+    if st["rounds_recorded"] <= 256:
+        assert sum(st["delta_rows"]) == st["derived_tuples"]
+    ctx.close()
