@@ -1372,6 +1372,27 @@ struct Runner {
     hr->dict_src = src;
   }
 
+  // Candidates follow the driver's rows: keys that are the leading columns of
+  // a finished driver in canonical order ascend as they are.
+  bool keys_lead(const RulePlan& p) {
+    bool lead = p.driver->sorted && !p.driver_delta && !head_of(p.driver);
+    for (int j = 0; j < p.nkey; ++j)
+      lead = lead && p.driver_act[j].kind == CA_BIND && p.driver_act[j].slot == p.key_slot[j];
+    return lead;
+  }
+
+  // Every driver column is a key (or fixed by a constant or another column), so
+  // no two of its rows make the same candidate.
+  static bool keys_cover_driver(const RulePlan& p) {
+    for (int j = 0; j < p.driver->arity; ++j) {
+      const ColAct& a = p.driver_act[j];
+      bool kept = a.kind == CA_CHECK_CONST || a.kind == CA_CHECK_SLOT;
+      for (int q = 0; q < p.nkey; ++q) kept = kept || (a.kind == CA_BIND && a.slot == p.key_slot[q]);
+      if (!kept) return false;
+    }
+    return true;
+  }
+
   xl_status setup_heads(Stratum& s) {
     joined_rows = 0;
     for (const RulePlan& p : s.variants)
@@ -1491,15 +1512,31 @@ struct Runner {
         // driver rows, so a sort of their keys replaces a bitmap that is far
         // larger than them (its clear, count and listing pass over every
         // word: 300 + 780 + 240 us for 1.25 GB holding 0.9 M rows, 80
-        // as candidate keys), or a hash table whose rows every read would sort.
-        bool scans = hr->once && h->nrows == 0 && c->index_mode == 0;
+        // as candidate keys), or a hash table whose rows every read would
+        // sort.  The table stays where rows may repeat (a driver column that
+        // is no key) and have to be sorted: it holds each once.  Rows turned
+        // from 10 M candidates, evaluate and read, us (table / sorted): all
+        // distinct 1035 / 812, a tenth of them 707 / 825, 1,000 rows 530 /
+        // 986; from 100,000 candidates 200 / 210, 172 / 212 and 119 / 217; in
+        // ascending order (no sort) 10 M take 250 and 219 sorted.  Up to 4,096
+        // candidates are sorted in one launch.
+        bool scans = hr->once && h->nrows == 0 && c->index_mode == 0, distinct = true;
         double rows = 0;
         for (const RulePlan& p : s.full) {
           scans = scans && p.head == h && p.steps.empty();
+          distinct = distinct && keys_cover_driver(p);
           rows += (double)p.driver->nrows;
         }
+        auto sorted_beats_table = [&]() {
+          const bool lead = s.full.size() == 1 && keys_lead(s.full[0]);
+          if ((lead ? 8 : 16) * rows > (double)(c->arena.capacity() - c->arena.in_use())) return false;  // no room
+          // a table of distinct candidates grows to eight slots of 16 bytes per
+          // row at most, or to 16 M slots, beside the one before it
+          const double table = 160 * rows + (272 << 20) + 16.0 * (double)((int64_t)1 << c->hash_min_log2);
+          return distinct || lead || rows <= 4096 || table > (double)c->arena.largest_free();
+        };
         if (scans && rows < 2147483648.0 &&
-            (total_bits / 8 > budget || total_bits / 8 > 33554432.0 + 160.0 * rows)) {
+            (total_bits / 8 > budget ? sorted_beats_table() : total_bits / 8 > 33554432.0 + 160.0 * rows)) {
           hr->sorted_set = true;
         } else if (total_bits / 8 <= budget) {
           hr->dense = true;
@@ -3446,11 +3483,7 @@ struct Runner {
         return XL_OK;
       }
       if (h->is_sortagg || h->sorted_set) {
-        // candidates follow the driver's rows, so keys that are the leading
-        // columns of a driver in canonical order ascend already
-        bool lead = p.driver->sorted && !p.driver_delta && !head_of(p.driver);
-        for (int j = 0; j < p.nkey; ++j)
-          lead = lead && p.driver_act[j].kind == CA_BIND && p.driver_act[j].slot == p.key_slot[j];
+        const bool lead = keys_lead(p);
         a.emit.mode = EM_MAT;
         a.emit.mat_packed = 1;
         int64_t total = 0;

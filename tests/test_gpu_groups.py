@@ -194,3 +194,42 @@ def test_receipt_after_many_passes(passes, profile):
     if st["rounds_recorded"] <= 256:
         assert sum(st["delta_rows"]) == st["derived_tuples"]
     ctx.close()
+
+
+PROJECTED_RULES = """
+lead(X,Y) :- e(X,Y,_).
+turned(Y,X) :- e(X,Y,_).
+both(X,Y) :- e(X,Y,_).
+both(Y,X) :- e(X,Y,_).
+fixed(Y,X) :- e(X,Y,5).
+twice(Z,X) :- e(X,X,Z).
+outer(Z,X) :- e(X,_,Z).
+"""
+
+
+@pytest.mark.parametrize("workspace", [64, 1024])
+@pytest.mark.parametrize("n", [1, 2049, 200_000])
+def test_scanned_sets_of_wider_drivers(n, workspace):
+    """Heads that drop a driver column (candidates repeat), fix one by a constant or
+    by another column, or keep rows in order, with much and little room."""
+    from paper_2609_27203_amd import xlh
+    print(f"case: sets of wider drivers n={n} workspace={workspace} MB", flush=True)
+    rng = np.random.default_rng(n)
+    a = np.r_[0, 2**31 - 2, rng.integers(0, 2**31 - 1, 40)].astype(np.int32)
+    x, y = a[rng.integers(0, len(a), (2, n))]
+    x[0], y[0] = 0, 2**31 - 2
+    z = rng.integers(0, 9, n).astype(np.int32)
+    ctx = xlh.Context(device=0, workspace_bytes=workspace << 20)
+    ctx.set_option("hash_min_log2", 12)
+    ctx.relation("e", ("i32", "i32", "i32")).load([x, y, z])
+    e = set(zip(x.tolist(), y.tolist(), z.tolist()))
+    want = {"lead": {(p, q) for p, q, _ in e}, "turned": {(q, p) for p, q, _ in e},
+            "both": {r for p, q, _ in e for r in ((p, q), (q, p))}, "fixed": {(q, p) for p, q, r in e if r == 5},
+            "twice": {(r, p) for p, q, r in e if p == q}, "outer": {(r, p) for p, _, r in e}}
+    for name in want:
+        ctx.relation(name, I)
+    stats = ctx.compile(PROJECTED_RULES).run()
+    for name, rows in want.items():
+        assert list(zip(*[c.tolist() for c in ctx.relations[name].read()])) == sorted(rows), name
+    assert stats["derived_tuples"] == stats["new_tuples_total"] == sum(len(r) for r in want.values())
+    ctx.close()
