@@ -325,8 +325,15 @@ struct RowPack {
 // greatest image (2 * MAXC words, cleared by the call).
 hipError_t col_bounds(const RowPack& r, int ncols, int64_t n, uint32_t* out, hipStream_t s);
 hipError_t pack_rows(const RowPack& r, int64_t n, void* key, bool wide, uint32_t* pay, hipStream_t s);
-// Payload order within runs of equal keys; *flag |= 1 when a run is too long.
-hipError_t sort_runs(const void* key, bool wide, uint32_t* pay, int64_t n, uint32_t* flag, hipStream_t s);
+// out: the payloads in order within runs of equal keys; *flag |= 1 when a run is
+// too long (out is void then).
+hipError_t order_runs(const void* key, bool wide, const uint32_t* pay, int64_t n, uint32_t* out, uint32_t* flag,
+                      hipStream_t s);
+// out[i] = (run of row i) << bits | (pay[i] - lo), off: runs before each row
+// tile; and the payloads back from them.
+hipError_t run_keys(const void* key, bool wide, const uint32_t* pay, int64_t n, const uint32_t* off, int bits,
+                    uint32_t lo, u64* out, hipStream_t s);
+hipError_t run_payloads(const u64* sorted, int64_t n, int bits, uint32_t lo, uint32_t* pay, hipStream_t s);
 // Distinct rows per tile of the sorted rows (row_tiles(n) counts), and the
 // rows written out: distinct ones at the tiles' offsets off, or (off null)
 // every row.

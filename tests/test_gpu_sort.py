@@ -237,3 +237,49 @@ def test_small_loads(name, n):
         print(f"case: small load {name} n={n} device={device} shift={shift}", flush=True)
         for g, w in zip(_load_and_read(types, cols, device, shift, 8 << 20), want):
             assert np.array_equal(g.view(np.uint32), w.view(np.uint32))
+
+
+@pytest.mark.parametrize("value", ["f32", "narrow", "few", "same"])
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("run", [1, 2, 63, 64, 65, 66, 129, 2047, 2049, 20_000])
+def test_payload_order_within_runs(run, wide, value):
+    """Rows that agree in all columns but the payload, in runs around the length
+    that is ordered by counting and around a tile of rows: keys of 32 and 64 bits."""
+    rng = np.random.default_rng(run)
+    n = 20_011
+    at = np.arange(n) // run
+    a = (at * (2**31 // (n // run + 2)) if wide else at * (2**12 // (n // run + 2) or 1) % 2**12)
+    b = rng.integers(0, 2**31 - 1 if wide else 2**12, at[-1] + 1)[at]
+    a, b = np.r_[0, 2**31 - 1 if wide else 2**12 - 1, a], np.r_[0, 2**31 - 1 if wide else 2**12 - 1, b]
+    v = {"f32": rng.standard_normal(n + 2), "narrow": rng.integers(-2**19, 2**19, n + 2),
+         "few": rng.integers(0, 3, n + 2) * 2**20, "same": np.where(np.arange(n + 2) < 2, 2**24, 7)}[value]
+    cols = [a.astype(np.int32), b.astype(np.int32), v.astype(np.float32 if value == "f32" else np.int32)]
+    order = rng.permutation(n + 2)
+    cols = [np.ascontiguousarray(c[order]) for c in cols]
+    types = ("i32", "i32", "f32" if value == "f32" else "i32")
+    want = _canonical_bits(cols)
+    for device in (False, True):
+        print(f"case: runs of {run} wide={wide} value={value} device={device}", flush=True)
+        for g, w in zip(_load_and_read(types, cols, device), want):
+            assert np.array_equal(g.view(np.uint32), w.view(np.uint32))
+
+
+def test_long_runs_in_a_workspace_that_holds_less():
+    """Smaller workspaces down to one that refuses the load: the rows are right or the call is refused."""
+    from paper_2609_27203_amd import xlh
+    types, make = WIDTHS["payload_long_run"]
+    cols = make(np.random.default_rng(2), 50_000)
+    want = _canonical_bits(cols)
+    refused = 0
+    for ws in [(1 << 20) + i * (1 << 17) for i in range(24)]:
+        print(f"case: long runs loaded in {ws} bytes", flush=True)
+        for device in (False, True):
+            try:
+                got = _load_and_read(types, cols, device, 0, ws)
+            except xlh.XlError as e:
+                assert e.status_name == "XL_RESOURCE_EXHAUSTED"
+                refused += 1
+                continue
+            for g, w in zip(got, want):
+                assert np.array_equal(g.view(np.uint32), w.view(np.uint32))
+    assert 0 < refused < 48
