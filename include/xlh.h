@@ -204,7 +204,9 @@ xl_status xl_context_create_static(int device, void* hip_stream, xl_context** ou
 
 /*
  * Tunables (key, value):
- *   "hash_min_log2"   log2 of the smallest hash table (default 22)
+ *   "hash_min_log2"   log2 of the smallest hash table (default 22); the tables of
+ *                     recursive set heads start with up to eight times as many
+ *                     slots, or eight per row that a rule copies into the head
  *   "index_mode"      0 = automatic, 1 = always open-addressing hash tables,
  *                     2 = prefer dense key-domain tables where they fit
  *   "profile"         1 = time the join kernels with HIP events (receipt

@@ -900,6 +900,8 @@ struct HeadRun {
   bool lean = false;  // the same for dense values (unless the receipt counts listed slots)
   bool sorted_set = false;  // set head of a scan: candidate keys, sorted and deduplicated at the end
   bool in_order = false;    // the candidates ascend as they are
+  int64_t sure_rows = 0;    // hash set head: rows of a rule that copies a finished relation
+  double growth = 1;        // of the delta over the last round of a batch
   KeyPack kp{};
   int bits0 = 1;      // width of the first packed key component
   double domain = 0;  // number of possible keys
@@ -1425,6 +1427,15 @@ struct Runner {
     return true;
   }
 
+  // Every row of the driver, a finished relation, is a row of the head.
+  static bool copies_driver(const Stratum& s, const RulePlan& p) {
+    bool all = p.steps.empty() && p.negs.empty() && keys_cover_driver(p);
+    for (const auto& ops : p.stage_ops) all = all && ops.empty();
+    for (int j = 0; j < p.driver->arity; ++j) all = all && p.driver_act[j].kind == CA_BIND;
+    for (const Relation* h : s.heads) all = all && h != p.driver;
+    return all;
+  }
+
   xl_status setup_heads(Stratum& s) {
     joined_rows = 0;
     for (const RulePlan& p : s.variants)
@@ -1594,6 +1605,9 @@ struct Runner {
                          total_bits / 8 * 3 <= budget && self_join_shape(s.variants);
         }
       }
+      if (hr->is_set && s.recursive)
+        for (const RulePlan& p : s.full)
+          if (p.head == h && copies_driver(s, p)) hr->sure_rows = std::max(hr->sure_rows, p.driver->nrows);
       hr->preloaded = (hr->is_set || hr->is_minmax) ? h->nrows : 0;
       XL_TRY(init_head(hr.get()));
       heads.push_back(std::move(hr));
@@ -1609,19 +1623,42 @@ struct Runner {
     return XL_OK;
   }
 
-  // First capacity of a head's hash table.  A recursive set head starts at
-  // eight slots per row of the largest relation its rules join (within 1/32 of
-  // the free workspace): batched rounds use as many wavefronts as a quarter of the
-  // slots allows, and a growth inserts every row again.  16 sources over
-  // 200,000 nodes and 800,000 edges, evaluate and read: 1.67 ms from 4 M slots,
-  // 1.30 from 8 M.  A smaller
-  // hash_min_log2 than the default asks for small tables.
+  // Slots for a recursive set head that fills: eight per row of the largest
+  // relation its rules join, within 64 times the smallest table and 1/32 of the
+  // free workspace.
+  int64_t filled_cap(const HeadRun* h) const {
+    if (!h->is_set || h->once) return 0;
+    return std::min({(int64_t)next_pow2((uint64_t)joined_rows * 8), (int64_t)64 << c->hash_min_log2,
+                     (int64_t)next_pow2(c->arena.largest_free() / 32 / 16 + 1) / 2});
+  }
+  // First capacity of a head's hash table: 2^hash_min_log2 slots, or four per
+  // expected row.  Batched rounds use as many wavefronts as a quarter of the
+  // slots allows, and a growth inside a batch runs a round and inserts every row
+  // again; but every slot is cleared, whatever the head ends with.  So a
+  // recursive set head starts at filled_cap only within eight times the smallest
+  // table or eight slots per row it is sure to get, and takes the rest where the
+  // next batch would fill half of what it has (widen).  Evaluate and read, us, ids
+  // over 2^31, from filled_cap / so: 39 rows from 12 M edges 795 / 640, from 30 M
+  // 1250 / 907; 16 sources over 3 M edges (12 M rows) 3110 / 3170, over 12 M
+  // (47 M rows) 11800 / 12200; 2 sources over 30 M (15 M rows) 4920 / 5710; chains
+  // of four edges, 12 M (30 M rows) 6130 / 6180.  From 4 M slots with growths 16
+  // sources over 0.8 M edges (3 M rows) take 2008 where these take 1200, over
+  // 12 M 18300.
   int64_t initial_cap(const HeadRun* h, int64_t expect) {
-    int64_t cap = (int64_t)1 << c->hash_min_log2;
-    if (h->is_set && !h->once && c->hash_min_log2 >= 22)
-      cap = std::max(cap, std::min((int64_t)next_pow2((uint64_t)joined_rows * 8),
-                                   (int64_t)next_pow2(c->arena.largest_free() / 32 / 16 + 1) / 2));
-    return (int64_t)std::max<uint64_t>(cap, next_pow2((uint64_t)std::max<int64_t>(expect, 1) * 4));
+    const int64_t cap = (int64_t)1 << c->hash_min_log2;
+    const int64_t full = std::max(8 * cap, (int64_t)next_pow2((uint64_t)h->sure_rows * 8));
+    return std::max({cap, std::min(full, filled_cap(h)),
+                     (int64_t)next_pow2((uint64_t)std::max<int64_t>(expect, 1) * 4)});
+  }
+  // Before a batch of `rounds`: its rows as the last round's delta and growth
+  // promise them, once there is a row per 64 slots (few rows multiply for a
+  // round or two only).
+  xl_status widen(HeadRun* h, int rounds) {
+    if (h->keys * 64 < h->cap) return XL_OK;
+    double rows = (double)h->keys, d = (double)(h->dend - h->dbeg);
+    for (int r = 0; r < rounds; ++r) rows += d *= h->growth;
+    const int64_t want = filled_cap(h);
+    return rows > 0.5 * (double)h->cap && want > h->cap ? grow(h, 0, want) : XL_OK;
   }
   int64_t joined_rows = 0;  // rows of the largest relation outside the stratum that a variant joins
 
@@ -1811,10 +1848,11 @@ struct Runner {
     return XL_OK;
   }
 
-  // Grow the head's table (and row list) so it holds at least `need` keys.
-  xl_status grow(HeadRun* h, int64_t need) {
-    int64_t ncap = h->cap * 4;
-    while (ncap / 2 < need || ncap - need < WAVE_SLACK * 4 * EMIT_GRID + 1024) ncap *= 2;
+  // Grow the head's table (and row list) so it holds at least `need` keys, or to
+  // `want` slots.
+  xl_status grow(HeadRun* h, int64_t need, int64_t want = 0) {
+    int64_t ncap = want ? want : h->cap * 4;
+    while (!want && (ncap / 2 < need || ncap - need < WAVE_SLACK * 4 * EMIT_GRID + 1024)) ncap *= 2;
     Buf nt;
     XL_TRY(alloc_table(h, ncap, &nt));
     HIP_TRY(c, hipMemsetAsync(c->dcounters, 0, 8 * CNT_N, c->stream));
@@ -2390,6 +2428,7 @@ struct Runner {
       // insert one batch: the grid takes at most a quarter of the smallest
       // table as slack (whatever the round's delta size, unknown here)
       int64_t waves = (int64_t)EMIT_GRID * 4;
+      for (auto& h : heads) XL_TRY(widen(h.get(), B));
       for (auto& h : heads) waves = std::min<int64_t>(waves, h->cap / 4 / WAVE_SLACK);
       waves = std::max<int64_t>(256, waves) / 4 * 4;
       batch_grid = (int)(waves / 4);
@@ -2476,8 +2515,11 @@ struct Runner {
       }
       if (done == K) {
         for (int q = 0; q < nh; ++q) {
-          heads[q]->dbeg = (int64_t)hbnd(q)[K];
-          heads[q]->dend = (int64_t)hbnd(q)[K + 1];
+          HeadRun* h = heads[q].get();
+          const double before = (double)(hbnd(q)[K] - hbnd(q)[K - 1]);
+          h->dbeg = (int64_t)hbnd(q)[K];
+          h->dend = (int64_t)hbnd(q)[K + 1];
+          h->growth = before > 0 ? (double)(h->dend - h->dbeg) / before : 1;
         }
         continue;
       }
