@@ -1188,9 +1188,9 @@ struct Runner {
         p.off = (uint32_t*)off;
         p.keys = (const uint32_t*)uk;
         p.key_range = nk;
-        // first segments by the key's high bits, about two buckets per key: a
-        // probe of evenly spread keys then searches one or two of them
-        // instead of all (200,000 distinct ids over 2^31, reachability rounds:
+        // first segments by the key's high bits, half a bucket to two per key: a
+        // probe of evenly spread keys then searches a few of them instead of all
+        // (200,000 distinct ids over 2^31, 262,144 buckets, reachability rounds:
         // 1098 -> 952 us).
         // Without room for the buckets every probe searches the whole list.
         const int bb = std::min(kbits, bitlen((uint64_t)nk));
