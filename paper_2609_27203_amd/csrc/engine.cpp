@@ -571,10 +571,10 @@ xl_status order_long_runs(Context* c, PackedRows* x, int64_t n, uint32_t most, u
 // The distinct rows of the loaded columns in canonical order, by one sort of
 // packed keys; a last column that is the payload is then ordered within the
 // runs of equal keys: by counting, or, where a run is too long for that, by a
-// second sort (8 M rows in runs of 200: 920 us; 2,050 column by column).  *done stays false when the
-// columns do not fit a key and a payload or when the workspace does not hold a
-// sort: the caller then sorts column by column.  Raw columns released by then
-// are all written again, in another row order.
+// second sort (8 M rows in runs of 200: 888 us; 2,050 column by column).  *done
+// stays false when the columns do not fit a key and a payload or when the
+// workspace does not hold a sort: the caller then sorts column by column.  Raw
+// columns released by then are all written again, in another row order.
 xl_status load_packed(Context* c, const Relation* r, const uint32_t* const* rc, Buf* raw, int64_t n,
                       const uint32_t* lo, const uint32_t* hi, Buf* fin, int64_t* m, bool* done) {
   *done = false;
@@ -616,21 +616,15 @@ xl_status load_packed(Context* c, const Relation* r, const uint32_t* const* rc, 
     return ctl_read(c, tot.p, x.has_pay ? 8 : 4, t);
   };
   if (x.has_pay) {
-    st = dalloc(c, (size_t)n * 4, &x.pay2, "sort payload");
-    if (st != XL_OK) return give_back(st);
     HIP_TRY(c, hipMemsetAsync(tot.p, 0, 8, c->stream));
-    HIP_TRY(c, k::order_runs(x.skey(), x.wide, x.spay(), n, x.pay2.as<uint32_t>(), tot.as<uint32_t>() + 1, c->stream));
-    std::swap(x.pay.p, x.pay2.p);
+    HIP_TRY(c, k::order_runs(x.skey(), x.wide, x.spay(), n, tot.as<uint32_t>() + 1, c->stream));
   }
   XL_TRY(count());
   if (t[1]) {
-    std::swap(x.pay.p, x.pay2.p);
-    x.pay2.reset();
     st = order_long_runs(c, &x, n, t[0], cnt.as<uint32_t>(), off.as<uint32_t>(), tmp.p, tot.as<uint32_t>());
     if (st != XL_OK) return give_back(st);
     XL_TRY(count());
   }
-  x.pay2.reset();
   *m = t[0];
   for (int j = 0; j < r->arity; ++j) {
     XL_TRY(dalloc(c, (size_t)*m * 4, &fin[j], "relation column"));

@@ -325,10 +325,9 @@ struct RowPack {
 // greatest image (2 * MAXC words, cleared by the call).
 hipError_t col_bounds(const RowPack& r, int ncols, int64_t n, uint32_t* out, hipStream_t s);
 hipError_t pack_rows(const RowPack& r, int64_t n, void* key, bool wide, uint32_t* pay, hipStream_t s);
-// out: the payloads in order within runs of equal keys; *flag |= 1 when a run is
-// too long (out is void then).
-hipError_t order_runs(const void* key, bool wide, const uint32_t* pay, int64_t n, uint32_t* out, uint32_t* flag,
-                      hipStream_t s);
+// Puts the payloads in order within runs of equal keys; *flag |= 1 when a run is
+// too long (that one and some others are left as they are then).
+hipError_t order_runs(const void* key, bool wide, uint32_t* pay, int64_t n, uint32_t* flag, hipStream_t s);
 // out[i] = (run of row i) << bits | (pay[i] - lo), off: runs before each row
 // tile; and the payloads back from them.
 hipError_t run_keys(const void* key, bool wide, const uint32_t* pay, int64_t n, const uint32_t* off, int bits,

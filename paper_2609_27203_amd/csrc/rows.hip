@@ -114,62 +114,62 @@ hipError_t pack_rows(const RowPack& r, int64_t n, void* key, bool wide, uint32_t
   return hipGetLastError();
 }
 
-// Rows of equal keys (sorted by key only) put into payload order.  Every row
-// finds its place in its run by counting the payloads before it that are not
-// greater and those after it that are less.  A workgroup orders 2,048 rows
-// from LDS with RW_RUN rows on both sides; neighbouring lanes compare
-// neighbouring words.  Bound by its traffic where runs are short (rows that
-// agree in all columns but the last are few), by the comparisons where they
-// are long: a row takes as many steps as its run has rows.  Loads of 8 M rows
-// (32 key bits, a float): 423 us without runs, 488 in runs of ten, 617 of 30
-// (one thread a run, sorting by insertion: 540 in runs of two, 925 of ten,
-// 4,080 of 40); 65 rows take longer than the second sort.
-// Runs of more than RW_RUN rows raise *flag and are left to run_keys below
-// (nothing of out is used then); the keys ascend, so two equal ones RW_RUN
-// apart tell.
-constexpr int RW_RUN = 64, RO_THREADS = 256, RO_ITEMS = 8, RO_TILE = RO_THREADS * RO_ITEMS;
+// Rows of equal keys (sorted by key only) put into payload order, in place.
+// Every row finds its place in its run by counting the payloads before it that
+// are not greater and those after it that are less.  A run belongs to the
+// workgroup in whose tile it starts, which alone uses and writes its payloads
+// (up to RW_RUN - 1 of them after the tile), from LDS; neighbouring lanes
+// compare neighbouring words.  Bound by its traffic where runs are short (rows
+// that agree in all columns but the last are few, and a row alone is not
+// written), by the comparisons where they are long: a row takes as many steps as
+// its run has rows.  Loads of 8 M rows (32 key bits, a float), us: no runs 418,
+// runs of ten 480, of 30 576, of 60 720 (one thread a run, sorting by insertion:
+// 408, 698, 1965 and 2997); 20,000 rows in runs of 40 141 (217).  512 rows a
+// workgroup: with 1,024 60,000 rows take 131 us, with 512 or 256 128, and 8 M
+// rows with 256 692, with more 684.
+// Runs of more than RW_RUN rows raise *flag, and their tile is left to run_keys
+// below; the keys ascend, so two equal ones RW_RUN apart tell.
+constexpr int RW_RUN = 64, RO_THREADS = 256, RO_ITEMS = 2, RO_TILE = RO_THREADS * RO_ITEMS;
 template <typename K>
-__global__ __launch_bounds__(RO_THREADS) void order_runs_k(const K* key, const uint32_t* pay, int64_t n,
-                                                           uint32_t* out, uint32_t* flag) {
-  __shared__ K s_k[RO_TILE + 2 * RW_RUN];
-  __shared__ uint32_t s_p[RO_TILE + 2 * RW_RUN];
-  const int64_t first = (int64_t)blockIdx.x * RO_TILE - RW_RUN;  // the row of LDS place 0
-  for (int q = threadIdx.x; q < RO_TILE + 2 * RW_RUN; q += RO_THREADS) {
-    const int64_t i = min(max(first + q, (int64_t)0), n - 1);
-    s_k[q] = key[i];
-    s_p[q] = pay[i];
+__global__ __launch_bounds__(RO_THREADS) void order_runs_k(const K* key, uint32_t* pay, int64_t n, uint32_t* flag) {
+  __shared__ K s_key[1 + RO_TILE + RW_RUN];  // from the row before the tile on
+  __shared__ uint32_t s_p[RO_TILE + RW_RUN];
+  K* s_k = s_key + 1;
+  const int64_t first = (int64_t)blockIdx.x * RO_TILE;
+  const int have = (int)min((int64_t)(RO_TILE + RW_RUN), n - first);  // rows in LDS
+  for (int q = threadIdx.x; q < have; q += RO_THREADS) {
+    s_k[q] = key[first + q];
+    s_p[q] = pay[first + q];
   }
+  if (threadIdx.x == 0) s_k[-1] = first > 0 ? key[first - 1] : 0;
   __syncthreads();
   bool over = false;
 #pragma unroll
   for (int t = 0; t < RO_ITEMS; ++t) {
-    const int q = RW_RUN + t * RO_THREADS + (int)threadIdx.x;
-    over = over || (first + q < n && first + q >= RW_RUN && s_k[q - RW_RUN] == s_k[q]);
+    const int q = t * RO_THREADS + (int)threadIdx.x;
+    over = over || (q + RW_RUN < have && s_k[q] == s_k[q + RW_RUN]);
   }
   if (__syncthreads_or(over)) {
-    if (threadIdx.x == 0) atomicOr(flag, 1u);
+    // (read first: thousands of workgroups' atomics on one word are served one after another)
+    if (threadIdx.x == 0 && !__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(flag, 1u);
     return;
   }
-  for (int t = 0; t < RO_ITEMS; ++t) {
-    const int q = RW_RUN + t * RO_THREADS + (int)threadIdx.x;
-    const int64_t i = first + q;
-    if (i >= n) break;
+  for (int q = threadIdx.x; q < have; q += RO_THREADS) {
     const K k = s_k[q];
     const uint32_t x = s_p[q];
-    const int back = (int)min((int64_t)RW_RUN, i), ahead = (int)min((int64_t)RW_RUN, n - 1 - i);
-    int place = 0, j = 1;
-    for (; j <= back && s_k[q - j] == k; ++j) place += s_p[q - j] <= x ? 1 : 0;
-    const int before = j - 1;
-    for (j = 1; j <= ahead && s_k[q + j] == k; ++j) place += s_p[q + j] < x ? 1 : 0;
-    out[i - before + place] = x;
+    int start = q, place = 0;
+    for (; start > 0 && s_k[start - 1] == k; --start) place += s_p[start - 1] <= x ? 1 : 0;
+    if (start >= RO_TILE || (start == 0 && first > 0 && s_k[-1] == k)) continue;  // another tile's run
+    int end = q + 1;
+    for (; end < have && s_k[end] == k; ++end) place += s_p[end] < x ? 1 : 0;
+    if (end - start > 1) pay[first + start + place] = x;
   }
 }
-hipError_t order_runs(const void* key, bool wide, const uint32_t* pay, int64_t n, uint32_t* out, uint32_t* flag,
-                      hipStream_t s) {
+hipError_t order_runs(const void* key, bool wide, uint32_t* pay, int64_t n, uint32_t* flag, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const unsigned g = (unsigned)((n + RO_TILE - 1) / RO_TILE);
-  if (wide) order_runs_k<u64><<<g, RO_THREADS, 0, s>>>((const u64*)key, pay, n, out, flag);
-  else order_runs_k<uint32_t><<<g, RO_THREADS, 0, s>>>((const uint32_t*)key, pay, n, out, flag);
+  const unsigned g = grid_for(n, RO_TILE, 1 << 30);
+  if (wide) order_runs_k<u64><<<g, RO_THREADS, 0, s>>>((const u64*)key, pay, n, flag);
+  else order_runs_k<uint32_t><<<g, RO_THREADS, 0, s>>>((const uint32_t*)key, pay, n, flag);
   return hipGetLastError();
 }
 
