@@ -6,8 +6,8 @@
 // unpacked (and deduplicated) straight into the columns.  Every kernel here is
 // bound by its traffic.  Loading 8 M rows (i32, i32, f32: 40 key bits and a
 // payload) takes 5 radix passes of 12-byte records instead of 12 passes of
-// (key, row number) pairs and as many random gathers: 1.74 -> 0.66 ms of
-// kernels (five passes 0.41, run sort 0.09, pack 0.04, count and unpack 0.06,
+// (key, row number) pairs and as many random gathers: 1.74 -> 0.60 ms of
+// kernels (five passes 0.41, runs ordered 0.05, pack 0.04, count and unpack 0.06,
 // bounds 0.03).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
