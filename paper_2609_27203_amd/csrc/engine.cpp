@@ -1141,6 +1141,11 @@ struct Runner {
       p.keys = nullptr;
       p.key_lo = 0;
       p.key_range = 0;
+      if (order_col >= 0 && order_kind == 0) {  // (no key, so never read)
+        void* fp;
+        XL_TRY(own(4, "index first rows", &fp));
+        ix->first = (uint32_t*)fp;
+      }
     } else {
       if (rel->types[col] != T_I32) return c->fail(XL_UNSUPPORTED, "index key columns must be int32");
       const int64_t range = (int64_t)khi - klo + 1;

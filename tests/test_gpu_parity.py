@@ -921,6 +921,23 @@ def test_closure_whose_seed_derives_nothing(resident):
     assert stats["iterations"] == 0
 
 
+
+@pytest.mark.parametrize("resident", [0, 1])
+def test_closure_joined_with_an_empty_relation(resident):
+    """The seed comes from another relation than the one the rounds join, which
+    has no row: one pass that derives nothing."""
+    edb = _edges([1, 2, 3, 70], [2, 3, 4, 1])
+    edb["first"] = edb.pop("edge")
+    edb["edge"] = (("i32", "i32"), [np.zeros(0, np.int32)] * 2)
+    wl = W.Workload("empty_step", "path(X, Y) :- first(X, Y).\npath(X, Z) :- path(X, Y), edge(Y, Z).", edb,
+                    {"path": ("i32", "i32")})
+    print(f"case: closure joined with an empty relation resident={resident}", flush=True)
+    ref = evaluate(wl.rules, wl.edb, wl.idb)
+    rels, stats, _ = engine_run(wl, options={"frontier_resident": resident}, workspace_bytes=256 << 20)
+    _compare(wl, rels, ref)
+    assert stats["iterations"] == len(ref.sizes["path"]) - 1
+
+
 def test_self_loop_and_duplicates():
     wl = W.Workload("loops", W.TC_RULES, _edges([0, 0, 1, 1, 2], [0, 1, 2, 2, 0]), {"path": ("i32", "i32")})
     ref = evaluate(wl.rules, wl.edb, wl.idb)
