@@ -223,6 +223,8 @@ struct StageArgs {
 struct DensePullArgs {
   const uint32_t* list;   // marked delta slots, ascending
   uint32_t* mark;         // or (batched rounds) the mark words themselves
+  const uint32_t* long_rows;  // with mark: rows of rev in long lists (k::long_rows); above long_min, units are small
+  uint32_t long_min;
   int64_t n;              // listed keys, or slots covered by the mark words
   const uint32_t* dict;   // rank -> first key value
   uint32_t range1;

@@ -2923,7 +2923,7 @@ struct Runner {
     IndexProbe fwd{};
     XL_TRY(get_index(sp.rel, sp.key_col, &fwd, -1, nullptr, 0, true));
     const int B = c->batched_rounds;
-    Buf acc;
+    Buf acc, longs;
     XL_TRY(dalloc(c, (size_t)B * 8 * CNT_N, &acc, "round counters"));
     std::vector<hipEvent_t> evs;
     if (c->profile) {
@@ -2956,6 +2956,12 @@ struct Runner {
         XL_TRY(pull_args(p, h, fast, fcol, q));
         q.mark = h->dchg.as<uint32_t>();
         q.n = nsd;
+        if (!longs.p) {  // once per run: the rounds pull over the same index
+          XL_TRY(dalloc(c, 4, &longs, "rows in long lists"));
+          HIP_TRY(c, k::long_rows(q.rev, longs.as<uint32_t>(), c->stream));
+        }
+        q.long_rows = longs.as<uint32_t>();
+        q.long_min = (uint32_t)(sp.rel->nrows / 4);
         q.counters = acc.as<unsigned long long>() + (size_t)r * CNT_N;
         if (c->profile) HIP_TRY(c, hipEventRecord(evs[2 * r], c->stream));
         HIP_TRY(c, k::dense_pull_marks(q, c->stream));

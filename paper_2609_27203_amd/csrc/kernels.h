@@ -218,6 +218,7 @@ hipError_t dense_pull(const DensePullArgs& a, hipStream_t s);
 // The same over the marked slots of a.mark (a.n slots, a multiple of 32; a.fast
 // rules), which it clears; npres must be zero on entry.  CNT_APPENDED counts the
 // marked keys.
+hipError_t long_rows(const IndexProbe& e, uint32_t* rows, hipStream_t s);
 hipError_t dense_pull_marks(const DensePullArgs& a, hipStream_t s);
 // Marks (target-major, nrank a multiple of 32) of the keys that receive a
 // contribution from the delta presence bits pres, pushed through e's index by

@@ -2418,8 +2418,7 @@ __device__ __forceinline__ bool dense_merge(uint32_t* fval, uint32_t* fpres, uin
 typedef XL_KARG const DensePullArgs PullArgs;
 
 // Binds S, Z, Y and P1, then e's row e_row; false when the row does not
-// derive anything for this key.  FAST: the value is one add/subtract (a.fast).
-template <bool FAST>
+// derive anything for this key.
 __device__ __forceinline__ bool pull_bind(PullArgs& a, uint32_t r, uint32_t s, uint32_t y, uint32_t e_row,
                                           Regs& u) {
   const uint32_t z = a.rev.col[a.zcol][e_row];
@@ -2427,10 +2426,6 @@ __device__ __forceinline__ bool pull_bind(PullArgs& a, uint32_t r, uint32_t s, u
   if (zb >= a.range1) return false;
   const uint32_t zs = zb * a.nrank + r;
   if (!((a.cpres[zs >> 5] >> (zs & 31)) & 1u)) return false;
-  if constexpr (FAST) {
-    setv(u, a.val_slot, fast_value(a.fast, a.val_type, a.cval[zs], a.rev.col[a.fcol][e_row]));
-    return true;
-  }
   u = (Regs)(0u);
   setv(u, a.slot_s, s);
   setv(u, a.slot_z, z);
@@ -2566,7 +2561,7 @@ __device__ __forceinline__ uint32_t pull_fold(PullArgs& a, uint32_t t, bool act,
     for (uint32_t jj = 0; !FAST && jj < maxdeg; ++jj) {
       if (jj >= deg) continue;
       Regs u;
-      if (!pull_bind<FAST>(a, r, a.dict[r], y, e0 + jj, u)) continue;
+      if (!pull_bind(a, r, a.dict[r], y, e0 + jj, u)) continue;
       const uint32_t x = getv(u, a.val_slot);
       any = true;
       if (lse) {
@@ -2589,72 +2584,113 @@ __device__ __forceinline__ uint32_t pull_fold(PullArgs& a, uint32_t t, bool act,
   }
   L.excl[lane] = incl - deg;
   L.beg[lane] = e0;
-  L.key[lane] = t;
+  L.key[lane] = FAST ? t % a.nrank : t;
   L.m[lane] = __float_as_uint(-INFINITY);
   L.acc[lane] = 0u;
   L.any[lane] = 0u;
   wave_lds_sync();
-  for (uint32_t base = 0; base < total; base += 64) {
-    const uint32_t j = base + (uint32_t)lane;
-    const bool on = j < total;
-    int q = 0;
+  // Bound by the chain row -> presence -> value of scattered slots: a one-add
+  // value's loads are issued for four steps at a time and folded in order (500
+  // targets of 100 in-edges, 64 sources: 1900 -> 1825 us)
+  constexpr int FLY = FAST ? 4 : 1;
+  for (uint32_t base0 = 0; base0 < total; base0 += 64 * FLY) {
+    int qs[FLY];
+    bool oks_in[FLY];
+    uint32_t xs[FLY];
+    if constexpr (FAST) {
+      uint32_t zs[FLY], wv[FLY], pw[FLY];
 #pragma unroll
-    for (int step = 32; step > 0; step >>= 1)
-      if (L.excl[q + step] <= j) q += step;
-    bool ok = false;
-    uint32_t x = 0;
-    if (on) {
-      const uint32_t tq = L.key[q], r = tq % a.nrank;
-      Regs u;
-      ok = pull_bind<FAST>(a, r, a.dict[r], tq / a.nrank + (uint32_t)a.lo1, L.beg[q] + (j - L.excl[q]), u);
-      if (ok) x = getv(u, a.val_slot);
-    }
-    // runs of equal owners among the active lanes
-    const int qp = __shfl_up(q, 1, 64);
-    const u64 am = __ballot(on);
-    const u64 heads = __ballot(on && (lane == 0 || qp != q)) | ~am;
-    const int head = 63 - __clzll((long long)(heads & ((2ull << lane) - 1ull)));
-    const u64 above = heads & ~((2ull << lane) - 1ull);
-    const int tail = above ? __ffsll((long long)above) - 2 : 63;
-    const bool is_tail = on && tail == lane;
-    const int oks = seg_sum_scan<int>(ok ? 1 : 0, lane, head);
-    if (lse) {
-      const float xv = ok ? __uint_as_float(x) : -INFINITY;
-      const float mrun = __shfl(seg_max_scan(xv, lane, head), tail, 64);
-      const float ev = (ok && mrun != -INFINITY) ? expf(xv - mrun) : 0.0f;
-      const float srun = seg_sum_scan<float>(ev, lane, head);
-      if (is_tail && oks > 0) {
-        const float m = __uint_as_float(L.m[q]), acc = __uint_as_float(L.acc[q]);
-        float nm = m, nacc = acc;
-        if (mrun == INFINITY || m == INFINITY) {  // the value itself
-          nm = INFINITY;
-          nacc = 1.0f;
-        } else if (mrun != -INFINITY) {
-          if (mrun > m) {
-            nacc = (m == -INFINITY ? 0.0f : acc * expf(m - mrun)) + srun;
-            nm = mrun;
-          } else {
-            nacc = acc + srun * expf(mrun - m);
-          }
-        }
-        L.m[q] = __float_as_uint(nm);
-        L.acc[q] = __float_as_uint(nacc);
-        L.any[q] = 1u;
+      for (int f = 0; f < FLY; ++f) {
+        const uint32_t j = base0 + 64u * f + (uint32_t)lane;
+        qs[f] = 0;
+#pragma unroll
+        for (int step = 32; step > 0; step >>= 1)
+          if (L.excl[qs[f] + step] <= j) qs[f] += step;
+        const uint32_t row = L.beg[qs[f]] + (j - L.excl[qs[f]]);
+        const uint32_t zb = j < total ? a.rev.col[a.zcol][row] - (uint32_t)a.lo1 : 0xffffffffu;
+        wv[f] = j < total ? a.rev.col[a.fcol][row] : 0u;
+        zs[f] = zb < a.range1 ? zb * a.nrank + L.key[qs[f]] : 0xffffffffu;
       }
-    } else if (f32) {
-      const float srun = seg_sum_scan<float>(ok ? __uint_as_float(x) : 0.0f, lane, head);
-      if (is_tail && oks > 0) {
-        L.acc[q] = __float_as_uint(__fadd_rn(__uint_as_float(L.acc[q]), srun));
-        L.any[q] = 1u;
+#pragma unroll
+      for (int f = 0; f < FLY; ++f) pw[f] = zs[f] != 0xffffffffu ? a.cpres[zs[f] >> 5] : 0u;
+#pragma unroll
+      for (int f = 0; f < FLY; ++f) {
+        oks_in[f] = zs[f] != 0xffffffffu && ((pw[f] >> (zs[f] & 31)) & 1u);
+        xs[f] = oks_in[f] ? a.cval[zs[f]] : 0u;
       }
+#pragma unroll
+      for (int f = 0; f < FLY; ++f) xs[f] = oks_in[f] ? fast_value(a.fast, a.val_type, xs[f], wv[f]) : 0u;
     } else {
-      const uint32_t srun = seg_sum_scan<uint32_t>(ok ? x : 0u, lane, head);
-      if (is_tail && oks > 0) {
-        L.acc[q] += srun;
-        L.any[q] = 1u;
+      const uint32_t j = base0 + (uint32_t)lane;
+      int q = 0;
+#pragma unroll
+      for (int step = 32; step > 0; step >>= 1)
+        if (L.excl[q + step] <= j) q += step;
+      qs[0] = q;
+      oks_in[0] = false;
+      xs[0] = 0;
+      if (j < total) {
+        const uint32_t tq = L.key[q], r = tq % a.nrank;
+        Regs u;
+        oks_in[0] = pull_bind(a, r, a.dict[r], tq / a.nrank + (uint32_t)a.lo1, L.beg[q] + (j - L.excl[q]), u);
+        if (oks_in[0]) xs[0] = getv(u, a.val_slot);
       }
     }
-    wave_lds_sync();
+#pragma unroll
+    for (int f = 0; f < FLY; ++f) {
+      const uint32_t base = base0 + 64u * f;
+      if (base >= total) break;
+      const bool on = base + (uint32_t)lane < total;
+      const int q = qs[f];
+      const bool ok = oks_in[f];
+      const uint32_t x = xs[f];
+      // runs of equal owners among the active lanes
+      const int qp = __shfl_up(q, 1, 64);
+      const u64 am = __ballot(on);
+      const u64 heads = __ballot(on && (lane == 0 || qp != q)) | ~am;
+      const int head = 63 - __clzll((long long)(heads & ((2ull << lane) - 1ull)));
+      const u64 above = heads & ~((2ull << lane) - 1ull);
+      const int tail = above ? __ffsll((long long)above) - 2 : 63;
+      const bool is_tail = on && tail == lane;
+      const int oks = seg_sum_scan<int>(ok ? 1 : 0, lane, head);
+      if (lse) {
+        const float xv = ok ? __uint_as_float(x) : -INFINITY;
+        const float mrun = __shfl(seg_max_scan(xv, lane, head), tail, 64);
+        const float ev = (ok && mrun != -INFINITY) ? expf(xv - mrun) : 0.0f;
+        const float srun = seg_sum_scan<float>(ev, lane, head);
+        if (is_tail && oks > 0) {
+          const float m = __uint_as_float(L.m[q]), acc = __uint_as_float(L.acc[q]);
+          float nm = m, nacc = acc;
+          if (mrun == INFINITY || m == INFINITY) {  // the value itself
+            nm = INFINITY;
+            nacc = 1.0f;
+          } else if (mrun != -INFINITY) {
+            if (mrun > m) {
+              nacc = (m == -INFINITY ? 0.0f : acc * expf(m - mrun)) + srun;
+              nm = mrun;
+            } else {
+              nacc = acc + srun * expf(mrun - m);
+            }
+          }
+          L.m[q] = __float_as_uint(nm);
+          L.acc[q] = __float_as_uint(nacc);
+          L.any[q] = 1u;
+        }
+      } else if (f32) {
+        const float srun = seg_sum_scan<float>(ok ? __uint_as_float(x) : 0.0f, lane, head);
+        if (is_tail && oks > 0) {
+          L.acc[q] = __float_as_uint(__fadd_rn(__uint_as_float(L.acc[q]), srun));
+          L.any[q] = 1u;
+        }
+      } else {
+        const uint32_t srun = seg_sum_scan<uint32_t>(ok ? x : 0u, lane, head);
+        if (is_tail && oks > 0) {
+          L.acc[q] += srun;
+          L.any[q] = 1u;
+        }
+      }
+      wave_lds_sync();
+    }
   }
   if (act && !L.any[lane]) atomicOr(&a.counters[CNT_FATAL], 8ull);
   uint32_t out = L.acc[lane];
@@ -2841,7 +2877,7 @@ __global__ __launch_bounds__(DP_WAVES * 64) void dense_pull_k(DensePullArgs by_v
 }
 
 // Keys straight from the mark words (batched rounds of a one-add rule).  A
-// unit is eight consecutive words, whose presence its wavefront owns: the next
+// unit is eight (or two) consecutive words, whose presence its wavefront owns: the next
 // delta's words are the marks themselves and the full relation's take them in
 // with plain stores (every marked key gets a value), and the marks are
 // cleared.  64 marked slots at a time go to the fold: a full pair of words as
@@ -2851,12 +2887,20 @@ __global__ __launch_bounds__(DP_WAVES * 64) void dense_pull_k(DensePullArgs by_v
 // 800,000 words), so units are small and go round the wavefronts; one load
 // fetches a wavefront's next eight units, since most of them are empty (units
 // of 32 words: 95 us a launch, the work on a quarter of the wavefronts).
+// Where a quarter of the in-edges lie in lists of more than DP_LANE_MAX, 64
+// marks are a walk of their own, and a unit is two words: the four walks of
+// eight words followed one another while other wavefronts had none (400 targets
+// a layer, 40 in-edges each, 200 sources, evaluated without a read: 1500 us in
+// units of eight, 1057 of four, 828 of two; from a list 950.  2,000 a layer, 8
+// in-edges, 256 sources: 957, 1020 and 1096).  So it is where there are few words
+// (the 400 targets with 32 in-edges: 691, 618 and 584).
 // Bound by the chain in-edge -> delta presence -> delta value at four
 // wavefronts per SIMD, two slots per lane in flight (one slot at five: 797 us
 // per run).  256 sources x 100,000 targets, eight in-edges each,
 // per run of 20 launches: 1015 us (833 of them the pull, the rest the listing)
 // -> 764.
-constexpr int PM_WAVES = 4, PM_WORDS = 8;
+constexpr int PM_WAVES = 4, PM_WORDS = 8, PM_WORDS_LONG = 2;
+constexpr uint32_t PM_SMALL = 32768;  // mark words: eight or fewer a resident wavefront
 __global__ __launch_bounds__(PM_WAVES * 64, 4) void dense_pull_marks_k(DensePullArgs by_value) {
   (void)by_value;
   PullArgs& a = *(PullArgs*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -2870,10 +2914,13 @@ __global__ __launch_bounds__(PM_WAVES * 64, 4) void dense_pull_marks_k(DensePull
   uint32_t keys = 0, mine = 0, examined = 0;
   const uint32_t nw = (uint32_t)(a.n / 32);
   const uint32_t waves = gridDim.x * PM_WAVES, me = blockIdx.x * PM_WAVES + (uint32_t)w;
-  const uint32_t units = (nw + PM_WORDS - 1) / PM_WORDS;
-  for (uint32_t u0 = me; u0 < units; u0 += 8 * waves) {  // (units < 2^24, waves < 2^16)
-    // lane l holds word l & 7 of unit u0 + (l >> 3) * waves
-    const uint32_t wi = (u0 + (uint32_t)(lane >> 3) * waves) * PM_WORDS + (uint32_t)(lane & 7);
+  const bool longs = nw <= PM_SMALL || *a.long_rows > a.long_min;
+  const uint32_t sh = longs ? 1u : 3u, words = 1u << sh;  // of a unit
+  static_assert(PM_WORDS == 8 && PM_WORDS_LONG == 2, "their logarithms");
+  const uint32_t units = (nw + words - 1) >> sh;
+  for (uint32_t u0 = me; u0 < units; u0 += (64u >> sh) * waves) {  // (units < 2^26, waves < 2^16)
+    // lane l holds word l % words of unit u0 + l / words * waves
+    const uint32_t wi = ((u0 + ((uint32_t)lane >> sh) * waves) << sh) + ((uint32_t)lane & (words - 1));
     const uint32_t word = wi < nw ? a.mark[wi] : 0u;
     if (!__ballot(word != 0)) continue;
     uint32_t old = 0;
@@ -2900,7 +2947,7 @@ __global__ __launch_bounds__(PM_WAVES * 64, 4) void dense_pull_marks_k(DensePull
         if (a.nrank % 64 == 0 && __popcll(m) >= 32) {
           const uint32_t t0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t - (uint32_t)lane));
           bool two = false;
-          if (!(pr & 1) && t0 % a.nrank + 64 < a.nrank) {
+          if (!longs && !(pr & 1) && t0 % a.nrank + 64 < a.nrank) {
             const uint32_t mw2 = (uint32_t)__shfl((int)word, 2 * pr + 2 + (lane >> 5), 64);
             const bool on2[2] = {on, ((mw2 >> (lane & 31)) & 1u) != 0};
             if (__popcll(__ballot(on2[1])) >= 32) {
@@ -2990,13 +3037,31 @@ static hipError_t dense_pull_launch(const DensePullArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// *rows += the rows of the index's lists of more than DP_LANE_MAX rows.
+__global__ void long_rows_k(IndexProbe e, uint32_t* rows) {
+  uint32_t n = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)e.key_range;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const uint32_t deg = e.off[i + 1] - e.off[i];
+    n += deg > DP_LANE_MAX ? deg : 0u;
+  }
+  for (int k = 32; k > 0; k >>= 1) n += __shfl_xor(n, k, 64);
+  if (lane_id() == 0 && n) atomicAdd(rows, n);
+}
+hipError_t long_rows(const IndexProbe& e, uint32_t* rows, hipStream_t s) {
+  const hipError_t err = hipMemsetAsync(rows, 0, 4, s);
+  if (err != hipSuccess || e.key_range == 0) return err;
+  long_rows_k<<<grid_for(e.key_range, 256, 256), 256, 0, s>>>(e, rows);
+  return hipGetLastError();
+}
+
 hipError_t dense_pull_marks(const DensePullArgs& a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
-  if (!a.fast || !a.mark || a.n % 32 || a.n > (int64_t)0xffffffffll) return hipErrorInvalidValue;
+  if (!a.fast || !a.mark || !a.long_rows || a.n % 32 || a.n > (int64_t)0xffffffffll) return hipErrorInvalidValue;
   int cap = 0;
   const hipError_t e = resident_blocks(dense_pull_marks_k, PM_WAVES * 64, 0, &cap);
   if (e != hipSuccess) return e;
-  dense_pull_marks_k<<<grid_for(a.n / 32, PM_WAVES * PM_WORDS, cap), PM_WAVES * 64, 0, s>>>(a);
+  dense_pull_marks_k<<<grid_for(a.n / 32, PM_WAVES * PM_WORDS_LONG, cap), PM_WAVES * 64, 0, s>>>(a);
   return hipGetLastError();
 }
 
